@@ -18,6 +18,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "dev_common.hpp"
 
@@ -76,6 +77,17 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// 64 floats (lane l: src + l's own address) to 64 consecutive floats of LDS from dst on (wave-uniform),
+// without passing through registers; wait_lds_loads() before the barrier that publishes them.
+__device__ __forceinline__ void load_to_lds(const float *src, float *dst) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 4, 0, 0);
+}
+__device__ __forceinline__ void wait_lds_loads() {
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), the other counters left alone
+    asm volatile("" ::: "memory");
 }
 
 // Detector coordinates of the voxels of a tile, relative to a reference point of the tile.
@@ -260,8 +272,18 @@ __global__ __launch_bounds__(256) void k_bp_voxel(const TP *__restrict__ proj, T
 // perspective map sends the box into the convex hull of its corners' images, so the detector
 // window [floor(min a*) - 1, ...] x [floor(min b*) - 1, ...] of WW x HW pixels (sized on the host
 // from an analytic bound) holds every tap of every voxel of the tile.  The windows are copied
-// into LDS row by row (lanes on consecutive pixels, zeros outside the detector), and the voxels
-// read their bilinear taps there.  The per-voxel arithmetic is that of k_bp_voxel.
+// into LDS, and the voxels read their bilinear taps there.  The per-voxel arithmetic is that of
+// k_bp_voxel.
+//
+// FP32 windows that lie on the detector, most of them, are copied by direct global-to-LDS loads of 64
+// consecutive window floats, with each lane's pixel offset formed once for all views: no registers, no
+// conversions, no tests, where the row-by-row copy (other windows and 16-bit storage: lanes on
+// consecutive pixels, zeros off the detector) spends about 4.5 VALU instructions per 64 voxel views.
+// Bound: VALU issue (on this chip floor, fract, conversions, compares, selects and integer operations
+// cost nearly twice an FMA) and LDS reads.  With the copies, the row's conversion straight to an
+// address, and the lower row carried as an interpolated value (one select, no second interpolation):
+// FDK at 512^3 / 360 angles 21.0 -> 16.4 ms (2.9e12 voxel views per second), the FDK reconstruction at
+// 1024^3 / 180 angles 89.9 -> 67.3 ms, pseudo-matched at 512^3 25.6 -> 21.0 ms (bitwise the same).
 #ifndef CT_BPL_NZ
 #define CT_BPL_NZ 16
 #endif
@@ -282,12 +304,13 @@ constexpr int BPL_PN = CT_BPL_PITCH;       // row pitch of narrow windows (the c
 // PITCH: LDS row pitch (floats) of a window, a compile-time constant so that both rows of a
 // bilinear tap pair are one base address with immediate offsets.
 constexpr int BPL_G = 64;  // angles per group of tile references
+constexpr int BPL_SL = 4;  // staging loads per thread whose offsets are formed once
 static_assert(BPL_NZ * 256 <= BPL_FLOATS, "the staging window parks the accumulators");
 
 // 8 (FDK) or 7 (pseudo-matched) waves per SIMD: the taps are LDS reads one after another, so
 // their latency is hidden by the other waves rather than by reads kept in flight in one wave
-// (which the compiler would otherwise schedule, at 4 waves per SIMD: 22.1 against 28.6 ms for
-// the FDK backprojection at 512^3 / 360 angles)
+// (FDK at 512^3 / 360 angles with 8 / 7 / 6 waves 15.6 / 16.2 / 16.9 ms; pseudo-matched with
+// 7 / 6 / 5 waves 20.3 / 21.1 / 21.3 ms; the few spilled registers lie outside the voxel loop)
 #ifndef CT_BPL_WAVES
 #define CT_BPL_WAVES 8
 #endif
@@ -312,10 +335,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W == CT_BP_
     const float zl0 = ((float)kb - kr) * A.dz, zk0 = fmaf((float)kb, A.dz, A.z0);
     const int64_t psz = (int64_t)A.nu * A.nv;
     const int wsz = PITCH * HW;
-    const float lamax = (float)(WW - 2), lbmax = (float)(HW - 2);
+    // just below the last column and row that have a neighbour
+    const float lamax = (float)(WW - 2) + 0.999f, lbtop = (float)(HW - 2) + 0.999f;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const int lane = tid & 63;
+    // element n = tid + 256 m of a window is its pixel (n % PITCH, n / PITCH), as an offset on the detector
+    int soff[BPL_SL];
+#pragma unroll
+    for (int m = 0; m < BPL_SL; ++m) soff[m] = (tid + 256 * m) / PITCH * A.nu + (tid + 256 * m) % PITCH;
     float acc[BPL_NZ];
     for (int g0 = 0; g0 < A.nang; g0 += BPL_G) {
         const int ng = min(BPL_G, A.nang - g0);
@@ -381,20 +409,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W == CT_BP_
         for (int t0 = 0; t0 < ng; t0 += K) {
             const int nk = min(K, ng - t0);
             __syncthreads();  // the window is free (parked sums read back, or the last round's taps read)
-            // stage: wave w copies rows w, w + 4, ... of every window; lane = window column
             for (int q = 0; q < nk; ++q) {
-                const int u = org[t0 + q][0] + lane;
+                const int oa = __builtin_amdgcn_readfirstlane(org[t0 + q][0]);
+                const int ob = __builtin_amdgcn_readfirstlane(org[t0 + q][1]);
+                const TP *pv = proj + (int64_t)(g0 + t0 + q) * psz;
+                float *wq = win + q * wsz;
+                if constexpr (std::is_same<TP, float>::value) {
+                    if (oa >= 0 && ob >= 0 && oa + PITCH <= A.nu && ob + HW <= A.nv) {
+                        // the window lies on the detector: copied straight into LDS, 64 consecutive floats
+                        // of it per wave and load, each lane's pixel offset the same for every view
+                        const float *pq = pv + (int64_t)ob * A.nu + oa;
+#pragma unroll
+                        for (int m = 0; m < BPL_SL; ++m)
+                            if (tid + 256 * m < wsz) load_to_lds(pq + soff[m], wq + 256 * m + 64 * wave);
+                        for (int n = tid + 256 * BPL_SL; n < wsz; n += 256)
+                            load_to_lds(pq + (n / PITCH) * A.nu + n % PITCH, wq + (n - lane));
+                        continue;
+                    }
+                }
+                // wave w copies rows w, w + 4, ... of the window; lane = window column; zeros off the detector
+                const int u = oa + lane;
                 const bool uok = lane < WW && (unsigned)u < (unsigned)A.nu;
-                const TP *pq = proj + (int64_t)(g0 + t0 + q) * psz + u;
-                float *wq = win + q * wsz + lane;
-                const int ob = org[t0 + q][1];
+                const TP *pq = pv + u;
                 for (int r = wave; r < HW; r += 4) {
                     const int v = ob + r;
                     float val = 0.0f;
                     if (uok && (unsigned)v < (unsigned)A.nv) val = to_f(pq[(int64_t)v * A.nu]);
-                    if (lane < WW) wq[r * PITCH] = val;
+                    if (lane < WW) wq[r * PITCH + lane] = val;
                 }
             }
+            wait_lds_loads();
             __syncthreads();
             if (!live) continue;
             for (int q = 0; q < nk; ++q) {
@@ -402,11 +446,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W == CT_BP_
                 // window-local column coordinate, row coordinate at the reference height
                 float as, bq, mv, iL;
                 tile_local(R, lx, ly, A.DSD, A.inv_dv, as, bq, mv, iL);
-                const float af = floorf(as);
-                const float fa = as - af;
+                // window-local coordinates are positive (the window starts a pixel below the least of them)
+                const float fa = __builtin_amdgcn_fractf(as);
                 const float wa0 = 1.0f - fa, wa1 = fa;  // taps off the detector are zeros in the window
-                // window column clamped into the window (an exact integer in FP32)
-                const float la = __builtin_amdgcn_fmed3f(af, 0.0f, lamax);
+                const float la = __builtin_amdgcn_fmed3f(as, 0.0f, lamax);
                 float w = 0.0f, rxy2 = 0.0f, wpm = 0.0f;
                 if (W == CT_BP_FDK) {
                     const float qq = A.DSO * iL;
@@ -417,60 +460,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W == CT_BP_
                     rxy2 = sx * sx + sy * sy;
                     wpm = A.pm_const * iL * iL * iL;
                 }
-                // LDS byte offset of the window column (exact in FP32); the clamp keeps rows 0 .. HW - 2
-                const float cb = fmaf(la, 4.0f, (float)(q * wsz * 4));
-                const float cbmax = fmaf(lbmax, (float)(4 * PITCH), cb);
-                // row coordinate of voxel k of the run: b0 + k db, with db a few pixels at most
-                const float b0 = fmaf(zl0, mv, bq), db = A.dz * mv;
-                // with the run climbing less than one row per voxel, a voxel's lower tap row is the
-                // previous voxel's lower or upper row: only its upper row is read (the same taps)
+                const int cb = (q * wsz + (int)la) * 4;  // LDS byte offset of the window column
+                // row coordinate of voxel k of the run: b0 + k db, with db a few pixels at most; the run's
+                // rows are kept inside the window by its first and last voxel (its rows are monotonic in k)
+                const float db = A.dz * mv;
+                float b0 = __builtin_amdgcn_fmed3f(fmaf(zl0, mv, bq), 0.0f, fmaf((float)(1 - BPL_NZ), db, lbtop));
+                float zkq = zk0;
+                asm volatile("" : "+v"(zkq));  // the heights are formed where they are used, not kept for every view
+                auto weight = [&](int k) {
+                    if (W == CT_BP_FDK) return w;
+                    const float zk = fmaf((float)k, A.dz, zkq);
+                    return wpm * __builtin_amdgcn_sqrtf(fmaf(zk, zk, rxy2));
+                };
+                // With the run climbing less than one row per voxel, a voxel's lower tap row is the previous
+                // voxel's lower or upper row, whose value at this column is at hand: only the upper row is
+                // read and interpolated (the same taps).  The choice is each lane's own: waves that hold
+                // both kinds run both loops, each with its lanes alone in the LDS reads, which was faster
+                // than the second loop for all of them (15.6 against 16.8 ms at 512^3 / 360 angles).
+                auto row = [&](int k, int &off) {
+                    const float bs = fmaf((float)k, db, b0);
+                    off = (int)__umul24((unsigned)(int)bs, 4u * PITCH) + cb;
+                    return __builtin_amdgcn_fractf(bs);
+                };
                 if (db < 0.999f) {
-                    float l0 = 0.0f, l1 = 0.0f, u0 = 0.0f, u1 = 0.0f, offp = 0.0f;
+                    float v0 = 0.0f, v1 = 0.0f;
+                    int offp = 0;
 #pragma unroll
                     for (int k = 0; k < BPL_NZ; ++k) {
-                        const float bs = fmaf((float)k, db, b0);
-                        const float bf = floorf(bs);
-                        const float fb = bs - bf;
-                        const float off = __builtin_amdgcn_fmed3f(fmaf(bf, (float)(4 * PITCH), cb), cb, cbmax);
-                        const float *t = (const float *)((const char *)win + (int)off);
-                        if (k == 0) {
-                            l0 = t[0];
-                            l1 = t[1];
-                        } else {
-                            const bool up = off != offp;  // one row up (4 PITCH bytes) or the same row
-                            l0 = up ? u0 : l0;
-                            l1 = up ? u1 : l1;
-                        }
-                        u0 = t[PITCH];
-                        u1 = t[PITCH + 1];
+                        int off;
+                        const float fb = row(k, off);
+                        const float *t = (const float *)((const char *)win + off);
+                        if (k == 0)
+                            v0 = fmaf(wa1, t[1], wa0 * t[0]);
+                        else
+                            v0 = off != offp ? v1 : v0;  // one row up, or the same row
+                        v1 = fmaf(wa1, t[PITCH + 1], wa0 * t[PITCH]);
                         offp = off;
-                        const float v0 = fmaf(wa1, l1, wa0 * l0);
-                        const float v1 = fmaf(wa1, u1, wa0 * u0);
-                        const float v = fmaf(fb, v1 - v0, v0);
-                        float wk = w;
-                        if (W != CT_BP_FDK) {
-                            const float zk = fmaf((float)k, A.dz, zk0);
-                            wk = wpm * __builtin_amdgcn_sqrtf(fmaf(zk, zk, rxy2));
-                        }
-                        acc[k] = fmaf(wk, v, acc[k]);
+                        acc[k] = fmaf(weight(k), fmaf(fb, v1 - v0, v0), acc[k]);
+                        // reads of a few voxels in flight at a time (more would spill)
+                        if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                     }
                 } else {
+                    // (b0 hidden from the compiler, which would otherwise form both loops' rows and offsets
+                    // before the branch and spill them)
+                    asm volatile("" : "+v"(b0), "+v"(rxy2));
 #pragma unroll
                     for (int k = 0; k < BPL_NZ; ++k) {
-                        const float bs = fmaf((float)k, db, b0);
-                        const float bf = floorf(bs);
-                        const float fb = bs - bf;
-                        const float off = __builtin_amdgcn_fmed3f(fmaf(bf, (float)(4 * PITCH), cb), cb, cbmax);
-                        const float *t = (const float *)((const char *)win + (int)off);
+                        int off;
+                        const float fb = row(k, off);
+                        const float *t = (const float *)((const char *)win + off);
                         const float v0 = fmaf(wa1, t[1], wa0 * t[0]);
                         const float v1 = fmaf(wa1, t[PITCH + 1], wa0 * t[PITCH]);
-                        const float v = fmaf(fb, v1 - v0, v0);
-                        float wk = w;
-                        if (W != CT_BP_FDK) {
-                            const float zk = fmaf((float)k, A.dz, zk0);
-                            wk = wpm * __builtin_amdgcn_sqrtf(fmaf(zk, zk, rxy2));
-                        }
-                        acc[k] = fmaf(wk, v, acc[k]);
+                        acc[k] = fmaf(weight(k), fmaf(fb, v1 - v0, v0), acc[k]);
+                        if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
