@@ -620,7 +620,11 @@ constexpr int VA_G = 32;      // views per group of tile references
 #define CT_VA_K 8
 #endif
 constexpr int VA_K = CT_VA_K;  // views per staging round, at most
-constexpr int VA_PN = 41, VA_PW = 65;
+// row pitches (records) of the windows: the narrowest that holds the window's columns is taken, since a
+// wider row leaves fewer of them in the buffer (49 / 41 / 31 rows).  A C-arm scan of a 200^3 grid needs
+// 48 columns by 33 rows, which only the middle pitch holds.
+constexpr int VA_PN = 41, VA_PM = 49, VA_PW = 65;
+inline int va_pitch(int ww) { return ww <= VA_PN ? VA_PN : ww <= VA_PM ? VA_PM : VA_PW; }
 
 template <typename TP, typename TV, int PITCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_adj_views_lds(const TP *__restrict__ proj, TV *__restrict__ vol, VArgs A, int WW,
@@ -976,7 +980,7 @@ void va_window(ct_plan *p, int &WW, int &HW) {
     std::lock_guard<std::mutex> lk(p->mu);
     if (p->va_ww < 0) {
         window_bound(p, VB_NZ, true, WW, HW);
-        if (WW > VA_PW || HW > VA_REC / (WW <= VA_PN ? VA_PN : VA_PW)) WW = HW = 0;
+        if (WW > VA_PW || HW > VA_REC / va_pitch(WW)) WW = HW = 0;
         p->va_ww = WW;
         p->va_hw = HW;
     }
@@ -1056,15 +1060,16 @@ ct_status launch_backproject_views(ct_plan *p, ct_backprojector kind, const void
         int AW = 0, AH = 0;
         va_window(p, AW, AH);
         if (AW > 0 && views_adjoint_mode() != 1) {
-            if (AW <= VA_PN) {
-                CT_DISPATCH2(pt, TP, vt, TV,
-                             hipLaunchKernelGGL((k_adj_views_lds<TP, TV, VA_PN>), grid, block, 0, st, (const TP *)proj,
-                                                (TV *)vol, A, AW, AH));
-            } else {
-                CT_DISPATCH2(pt, TP, vt, TV,
-                             hipLaunchKernelGGL((k_adj_views_lds<TP, TV, VA_PW>), grid, block, 0, st, (const TP *)proj,
-                                                (TV *)vol, A, AW, AH));
+#define CT_VA(PITCH)                                                                                              \
+    CT_DISPATCH2(pt, TP, vt, TV,                                                                                  \
+                 hipLaunchKernelGGL((k_adj_views_lds<TP, TV, PITCH>), grid, block, 0, st, (const TP *)proj, (TV *)vol, \
+                                    A, AW, AH))
+            switch (va_pitch(AW)) {
+                case VA_PN: CT_VA(VA_PN); break;
+                case VA_PM: CT_VA(VA_PM); break;
+                default: CT_VA(VA_PW); break;
             }
+#undef CT_VA
         } else {
             CT_DISPATCH2(pt, TP, vt, TV,
                          hipLaunchKernelGGL((k_adj_views<TP, TV>), grid, block, 0, st, (const TP *)proj, (TV *)vol, A));
