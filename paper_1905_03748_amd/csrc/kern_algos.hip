@@ -3,11 +3,14 @@
 // OS-SART (SART with one angle per update when block = 1) and TV steepest descent.  Reductions use a fixed partition
 // (DOT_BLOCKS contiguous ranges, fixed wave/block trees, fixed final sum), so results are bitwise
 // repeatable regardless of what else shares the device.
+#include <algorithm>
+#include <cfloat>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <utility>
 
 #include "dev_common.hpp"
 
@@ -172,82 +175,195 @@ __global__ __launch_bounds__(256) void k_sart_resid_t(const TP *__restrict__ b, 
     }
 }
 
-// TV_eps gradient with forward differences, unit spacing, zero difference at the last index.
+// TV_eps gradient with forward differences, unit spacing, zero difference at the last index:
+//   g = p_x(i - 1) - p_x + p_y(j - 1) - p_y + p_z(k - 1) - p_z,  p = D x / sqrt(|D x|^2 + eps).
 // Slices kg0 .. kg0 + nk - 1 of the volume (nz slices in all); x holds slices from kx0 on (at least
-// z - 1 .. z + 1 where they exist) and g from kg0 on.  A whole resident volume has kx0 = kg0 = 0.
-// Each thread walks TV_ZR slices of one (i, j) column: a voxel's gradient reads seven positions of
-// its own slice, three of the slice above and three of the one below, so the thread loads the
-// seven positions of each slice once and carries them up the column (7 loads per voxel, not 13).
-constexpr int TV_ZR = 8;
+// z - 1 .. z + 1 where they exist).  A whole resident volume has kx0 = kg0 = 0.
+//
+// A step needs ||g|| before it can move x, so it makes two passes, each forming g from x in registers:
+// k_tv_norm sums g^2 (reads x), k_tv_apply writes x - a g to another array (reads x, writes it): 12 bytes
+// of memory traffic per voxel and step, where a stored gradient took 24 (write g, read it for the norm,
+// read g and x, write x).  Each thread walks a run of slices of one (i, j) column: a voxel's gradient reads
+// seven positions of its own slice and three of the next, so the thread loads the seven positions of
+// each slice once and carries them up the column, with p_z of the slice below.  Positions past an
+// edge of the volume read the edge voxel, so their differences are zero without a test.  The
+// reciprocal square roots are the hardware's (1 ulp; a square root and a division each took about 25
+// instructions, four pairs per voxel): s >= eps, so a normal eps keeps them from denormal arguments, and
+// TINY serves an eps below FLT_MIN.  Bound: HBM and the address unit (7 loads of 4.7 cycles per wave and
+// slice) about evenly.
+// Five steps at 512^3 (with the copy of the image): 5.85 -> 2.90 ms.
+constexpr int TV_TY = 8;               // rows of a tile (waves of a block); a tile is 64 columns wide
+constexpr int TV_THREADS = 64 * TV_TY;
 struct TvPlane {
     float c, e, n, w, wn, s, se;  // (i, j), (i + 1, j), (i, j + 1), (i - 1, j), (i - 1, j + 1), (i, j - 1), (i + 1, j - 1)
 };
-__global__ __launch_bounds__(256) void k_tv_grad(const float *__restrict__ x, float *__restrict__ g, int nx, int ny,
-                                                 int nz, float eps, int64_t kx0, int64_t kg0, int64_t nk) {
-    const int i = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int j = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (i >= nx || j >= ny) return;
-    const int64_t sy = nx, sz = (int64_t)nx * ny;
-    const bool hx = i < nx - 1, hy = j < ny - 1, lx = i > 0, ly = j > 0;
-    auto plane = [&](int64_t k) {  // positions outside the volume's x-y extent read as 0 (unused)
-        const int64_t o = (k - kx0) * sz + (int64_t)j * sy + i;
-        TvPlane p;
-        p.c = x[o];
-        p.e = hx ? x[o + 1] : 0.0f;
-        p.n = hy ? x[o + sy] : 0.0f;
-        p.w = lx ? x[o - 1] : 0.0f;
-        p.wn = (lx && hy) ? x[o - 1 + sy] : 0.0f;
-        p.s = ly ? x[o - sy] : 0.0f;
-        p.se = (ly && hx) ? x[o - sy + 1] : 0.0f;
-        return p;
+struct TvArgs {
+    int nx, ny, nz;
+    float eps;
+    int64_t kx0, kg0, nk;
+    int zr;               // slices of a run
+    unsigned bx, by, bz;  // tiles along each axis
+};
+template <bool TINY>
+__device__ __forceinline__ float tv_rsqrt(float s) {
+    return TINY ? 1.0f / sqrtf(s) : __builtin_amdgcn_rsqf(s);
+}
+// visit(offset in x, x, g) for every voxel of the thread's run in the tile
+template <bool TINY, typename F>
+__device__ __forceinline__ void tv_walk(const float *__restrict__ x, const TvArgs &A, unsigned tx, unsigned ty,
+                                        unsigned tz, F visit) {
+    const int i = (int)tx * 64 + ((int)threadIdx.x & 63);
+    const int j = (int)ty * TV_TY + ((int)threadIdx.x >> 6);
+    if (i >= A.nx || j >= A.ny) return;
+    const int64_t sz = (int64_t)A.nx * A.ny;
+    const int oe = i < A.nx - 1 ? 1 : 0, ow = i > 0 ? -1 : 0;
+    const int on = j < A.ny - 1 ? A.nx : 0, os = j > 0 ? -A.nx : 0;
+    const int64_t r0 = (int64_t)tz * A.zr, r1 = min(r0 + (int64_t)A.zr, A.nk);
+    const int64_t k0 = A.kg0 + r0;
+    const float *p = x + (k0 - A.kx0) * sz + (int64_t)j * A.nx + i;
+    auto plane = [&](const float *q) {
+        TvPlane v;
+        v.c = q[0];
+        v.e = q[oe];
+        v.n = q[on];
+        v.w = q[ow];
+        v.wn = q[ow + on];
+        v.s = q[os];
+        v.se = q[os + oe];
+        return v;
     };
-    const int64_t r0 = (int64_t)blockIdx.z * TV_ZR, r1 = min(r0 + (int64_t)TV_ZR, nk);
-    int64_t k = kg0 + r0;
-    TvPlane pm = {}, pn = {};
-    if (k > 0) pm = plane(k - 1);
-    TvPlane pc = plane(k);
-    for (int64_t r = r0; r < r1; ++r, ++k) {
-        const bool hz = k < nz - 1;
-        if (hz) pn = plane(k + 1);
-        const float xc = pc.c;
-        // differences at the voxel
-        const float dxc = hx ? pc.e - xc : 0.0f;
-        const float dyc = hy ? pc.n - xc : 0.0f;
-        const float dzc = hz ? pn.c - xc : 0.0f;
-        float gv = -(dxc + dyc + dzc) / sqrtf(dxc * dxc + dyc * dyc + dzc * dzc + eps);
-        if (lx) {  // neighbour - e_x
-            const float xm = pc.w;
-            const float a = xc - xm;
-            const float b = hy ? pc.wn - xm : 0.0f;
-            const float c = hz ? pn.w - xm : 0.0f;
-            gv += a / sqrtf(a * a + b * b + c * c + eps);
-        }
-        if (ly) {
-            const float xm = pc.s;
-            const float a = hx ? pc.se - xm : 0.0f;
-            const float b = xc - xm;
-            const float c = hz ? pn.s - xm : 0.0f;
-            gv += b / sqrtf(a * a + b * b + c * c + eps);
-        }
-        if (k > 0) {
-            const float xm = pm.c;
-            const float a = hx ? pm.e - xm : 0.0f;
-            const float b = hy ? pm.n - xm : 0.0f;
-            const float c = xc - xm;
-            gv += c / sqrtf(a * a + b * b + c * c + eps);
-        }
-        g[(k - kg0) * sz + (int64_t)j * sy + i] = gv;
-        pm = pc;
+    TvPlane pc = plane(p);
+    float pz = 0.0f;  // p_z of the slice below
+    if (k0 > 0) {
+        const float *q = p - sz;
+        const float c = q[0], dx = q[oe] - c, dy = q[on] - c, dz = pc.c - c;
+        pz = dz * tv_rsqrt<TINY>(fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, A.eps))));
+    }
+    for (int64_t r = r0; r < r1; ++r, p += sz) {
+        const TvPlane pn = A.kg0 + r < A.nz - 1 ? plane(p + sz) : pc;
+        const float c = pc.c;
+        const float dx = pc.e - c, dy = pc.n - c, dz = pn.c - c;
+        const float q = tv_rsqrt<TINY>(fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, A.eps))));
+        const float wx = c - pc.w, wy = pc.wn - pc.w, wz = pn.w - pc.w;
+        const float qw = tv_rsqrt<TINY>(fmaf(wx, wx, fmaf(wy, wy, fmaf(wz, wz, A.eps))));
+        const float sx = pc.se - pc.s, sy = c - pc.s, sz_ = pn.s - pc.s;
+        const float qs = tv_rsqrt<TINY>(fmaf(sx, sx, fmaf(sy, sy, fmaf(sz_, sz_, A.eps))));
+        const float g = fmaf(-(dx + dy + dz), q, fmaf(wx, qw, fmaf(sy, qs, pz)));
+        visit(p - x, c, g);
+        pz = dz * q;
         pc = pn;
     }
 }
 
-// gradient of slices kg0 .. kg0 + nk - 1 (see k_tv_grad)
-static ct_status launch_tv_grad(const float *x, float *g, int nx, int ny, int nz, float eps, int64_t kx0, int64_t kg0,
-                                int64_t nk, hipStream_t st) {
-    if (nk <= 0) return CT_OK;
-    const dim3 grid((nx + 63) / 64, (ny + 3) / 4, (unsigned)((nk + TV_ZR - 1) / TV_ZR));
-    hipLaunchKernelGGL(k_tv_grad, grid, dim3(256), 0, st, x, g, nx, ny, nz, eps, kx0, kg0, nk);
+// Partial sums of g^2 (and, XX, of x^2) over the tiles, FP64: block b takes tiles b, b + gridDim.x, ...
+// and writes partials[b] (and partials[DOT_BLOCKS + b]).  COPY also writes x to y.
+template <bool TINY, bool XX, bool COPY>
+__global__ __launch_bounds__(TV_THREADS) void k_tv_norm(const float *__restrict__ x, TvArgs A, float *__restrict__ y,
+                                                        double *__restrict__ partials) {
+    __shared__ double lds[TV_TY];
+    double gg = 0.0, xx = 0.0;
+    const unsigned per = A.bx * A.by, n = per * A.bz;
+    for (unsigned t = blockIdx.x; t < n; t += gridDim.x)
+        tv_walk<TINY>(x, A, t % A.bx, t % per / A.bx, t / per, [&](int64_t o, float c, float g) {
+            gg = fma((double)g, (double)g, gg);
+            if (XX) xx = fma((double)c, (double)c, xx);
+            if (COPY) y[o] = c;
+        });
+    gg = block_sum(gg, lds);
+    if (threadIdx.x == 0) partials[blockIdx.x] = gg;
+    if (XX) {
+        xx = block_sum(xx, lds);
+        if (threadIdx.x == 0) partials[DOT_BLOCKS + blockIdx.x] = xx;
+    }
+}
+
+// TV scalars: [0] = ||x_in||^2, [1] = alpha, [2] = ||g||^2
+// The partial sums of k_tv_norm in a fixed order; with XX also alpha = lambda ||x_in||
+template <bool XX>
+__global__ __launch_bounds__(DOT_THREADS) void k_tv_sum(const double *__restrict__ partials, int n,
+                                                        double *__restrict__ scal, double lambda) {
+    __shared__ double lds[DOT_THREADS / 64];
+    double gg = 0.0, xx = 0.0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        gg += partials[i];
+        if (XX) xx += partials[DOT_BLOCKS + i];
+    }
+    gg = block_sum(gg, lds);
+    if (XX) xx = block_sum(xx, lds);
+    if (threadIdx.x == 0) {
+        scal[2] = gg;
+        if (XX) {
+            scal[0] = xx;
+            scal[1] = lambda * sqrt(xx);
+        }
+    }
+}
+
+// y = x - alpha g / ||g|| over the slices of A (x as it is when ||g|| is not positive); y holds slices
+// from ky0 on
+template <bool TINY>
+__global__ __launch_bounds__(TV_THREADS) void k_tv_apply(const float *__restrict__ x, float *__restrict__ y, TvArgs A,
+                                                         int64_t ky0, const double *__restrict__ scal) {
+    const double ng2 = scal[2];
+    const bool go = ng2 > 0.0;
+    const float a = go ? (float)(scal[1] / sqrt(ng2)) : 0.0f;
+    float *yo = y - (ky0 - A.kx0) * ((int64_t)A.nx * A.ny);
+    tv_walk<TINY>(x, A, blockIdx.x, blockIdx.y, blockIdx.z,
+                  [&](int64_t o, float c, float g) { yo[o] = go ? fmaf(-a, g, c) : c; });
+}
+
+TvArgs tv_args(int nx, int ny, int nz, double eps, int64_t kx0, int64_t kg0, int64_t nk) {
+    TvArgs A;
+    A.nx = nx;
+    A.ny = ny;
+    A.nz = nz;
+    A.eps = (float)eps;
+    A.kx0 = kx0;
+    A.kg0 = kg0;
+    A.nk = nk;
+    A.bx = (unsigned)((nx + 63) / 64);
+    A.by = (unsigned)((ny + TV_TY - 1) / TV_TY);
+    // a run's first slice costs 1.4 of the others, so runs are as long as still leaves 1024 blocks of 8
+    // waves (a full chip): 512^3 with runs of 32 / 16 / 8 / 4 slices 2.95 / 3.07 / 3.23 / 3.67 ms (5
+    // steps), 256^3 0.40 / 0.41 / 0.39 / 0.43, 101 x 97 x 90 0.148 / 0.105 / 0.094 / 0.088 (4 steps)
+    A.zr = 32;
+    while (A.zr > 4 && (int64_t)A.bx * A.by * ((nk + A.zr - 1) / A.zr) < 1024) A.zr /= 2;
+    A.bz = (unsigned)((nk + A.zr - 1) / A.zr);
+    return A;
+}
+bool tv_tiny(double eps) { return !((float)eps >= FLT_MIN); }
+
+// ||g||^2 of slices kg0 .. kg0 + nk - 1 into scal[2]; xx: also their ||x||^2 into scal[0] and
+// alpha = lambda ||x|| into scal[1]; copy (with xx): x to y.  partials: 2 DOT_BLOCKS doubles.
+ct_status launch_tv_norm(const float *x, const TvArgs &A, double eps, bool xx, float *y, double *partials, double *scal,
+                         double lambda, hipStream_t st) {
+    const int64_t tiles = (int64_t)A.bx * A.by * A.bz;
+    if (tiles > 0x7fffffff) return fail(CT_ERR_ARG, "TV: the image is too large");
+    const unsigned nb = (unsigned)std::min<int64_t>(tiles, DOT_BLOCKS);
+#define CT_TV_N(TI, XX_, CO) \
+    hipLaunchKernelGGL((k_tv_norm<TI, XX_, CO>), dim3(nb), dim3(TV_THREADS), 0, st, x, A, y, partials)
+    if (tv_tiny(eps)) {
+        if (xx && y) CT_TV_N(true, true, true);
+        else if (xx) CT_TV_N(true, true, false);
+        else CT_TV_N(true, false, false);
+    } else {
+        if (xx && y) CT_TV_N(false, true, true);
+        else if (xx) CT_TV_N(false, true, false);
+        else CT_TV_N(false, false, false);
+    }
+#undef CT_TV_N
+    CT_HIP(hipGetLastError());
+    if (xx) hipLaunchKernelGGL((k_tv_sum<true>), dim3(1), dim3(DOT_THREADS), 0, st, partials, (int)nb, scal, lambda);
+    else hipLaunchKernelGGL((k_tv_sum<false>), dim3(1), dim3(DOT_THREADS), 0, st, partials, (int)nb, scal, lambda);
+    CT_HIP(hipGetLastError());
+    return CT_OK;
+}
+
+ct_status launch_tv_apply(const float *x, float *y, const TvArgs &A, double eps, int64_t ky0, const double *scal,
+                          hipStream_t st) {
+    const dim3 grid(A.bx, A.by, A.bz);
+    if (tv_tiny(eps)) hipLaunchKernelGGL((k_tv_apply<true>), grid, dim3(TV_THREADS), 0, st, x, y, A, ky0, scal);
+    else hipLaunchKernelGGL((k_tv_apply<false>), grid, dim3(TV_THREADS), 0, st, x, y, A, ky0, scal);
     CT_HIP(hipGetLastError());
     return CT_OK;
 }
@@ -314,18 +430,6 @@ __global__ __launch_bounds__(256) void k_rof_u(float *__restrict__ x, const floa
 __global__ void k_fill_zero(float *__restrict__ p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0.0f;
-}
-
-// TV scalars: [0] = ||x_in||^2, [1] = alpha, [2] = ||g||^2
-__global__ void k_tv_alpha(double *scal, double lambda) { scal[1] = lambda * sqrt(scal[0]); }
-
-__global__ void k_tv_update(float *__restrict__ x, const float *__restrict__ g, const double *__restrict__ scal,
-                            int64_t n) {
-    const double ng2 = scal[2];
-    if (!(ng2 > 0.0)) return;
-    const float a = (float)(scal[1] / sqrt(ng2));
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        x[i] = fmaf(-a, g[i], x[i]);
 }
 
 struct Workspace {
@@ -549,7 +653,7 @@ ct_status sart_run(ct_plan *p, const void *b, ct_dtype pt, void *x, ct_dtype vt,
 size_t tv_workspace(const ct_geometry &g, ct_dtype vt) {
     const size_t nv = (size_t)g.nVoxel[0] * g.nVoxel[1] * g.nVoxel[2];
     // a 16-bit image is stepped in an FP32 copy
-    return align256(nv * 4) * (vt == CT_F32 ? 1 : 2) + align256(DOT_BLOCKS * 8) + align256(4 * 8);
+    return align256(nv * 4) * (vt == CT_F32 ? 1 : 2) + align256(2 * DOT_BLOCKS * 8) + align256(4 * 8);
 }
 
 ct_status tv_run(const ct_geometry &g, void *xs, ct_dtype vt, int32_t nsteps, double lambda, double eps, void *work,
@@ -559,24 +663,27 @@ ct_status tv_run(const ct_geometry &g, void *xs, ct_dtype vt, int32_t nsteps, do
     Workspace ws;
     ct_status s = ws.acquire(work, tv_workspace(g, vt), st);
     if (s != CT_OK) return s;
-    float *gbuf = (float *)ws.take(nv * 4);
-    double *parts = (double *)ws.take(DOT_BLOCKS * 8);
+    float *buf = (float *)ws.take(nv * 4);
+    double *parts = (double *)ws.take(2 * DOT_BLOCKS * 8);
     double *scal = (double *)ws.take(4 * 8);
-    void *x = xs;
+    float *x = (float *)xs;
     if (vt != CT_F32) {
-        x = ws.take(nv * 4);
+        x = (float *)ws.take(nv * 4);
         CK(convert(xs, vt, x, CT_F32, nv, st));
     }
-    CK(dot_f64(x, x, CT_F32, nv, scal + 0, parts, st));
-    hipLaunchKernelGGL(k_tv_alpha, dim3(1), dim3(1), 0, st, scal, lambda);
-    CT_HIP(hipGetLastError());
+    if (nsteps <= 0) return CT_OK;
+    const TvArgs A = tv_args(nx, ny, nz, eps, 0, 0, nz);
+    // the steps alternate between the two arrays; with an odd number of them on an FP32 image the first
+    // norm pass copies x, so that the last step writes the caller's array
+    const bool copy = vt == CT_F32 && (nsteps & 1);
+    float *src = copy ? buf : x, *dst = copy ? x : buf;
     for (int32_t k = 0; k < nsteps; ++k) {
-        CK(launch_tv_grad((const float *)x, gbuf, nx, ny, nz, (float)eps, 0, 0, nz, st));
-        CK(dot_f64(gbuf, gbuf, CT_F32, nv, scal + 2, parts, st));
-        hipLaunchKernelGGL(k_tv_update, dim3(ew_grid(nv)), dim3(EW_THREADS), 0, st, (float *)x, (const float *)gbuf, scal, nv);
-        CT_HIP(hipGetLastError());
+        if (k == 0) CK(launch_tv_norm(x, A, eps, true, copy ? buf : nullptr, parts, scal, lambda, st));
+        else CK(launch_tv_norm(src, A, eps, false, nullptr, parts, scal, lambda, st));
+        CK(launch_tv_apply(src, dst, A, eps, 0, scal, st));
+        std::swap(src, dst);
     }
-    if (vt != CT_F32) CK(convert(x, CT_F32, xs, vt, nv, st));
+    if (vt != CT_F32) CK(convert(src, CT_F32, xs, vt, nv, st));
     return CT_OK;
 #undef CK
 }
@@ -666,7 +773,7 @@ ct_status tv_host_run(const ct_geometry &g, float *hx, int32_t nsteps, double la
     const int64_t slice = (int64_t)nx * ny;
     const uint64_t sb = (uint64_t)slice * sizeof(float);
     const uint64_t fixed = TV_RESERVE + align256(DOT_BLOCKS * 8) + align256(4 * 8);
-    // device: the slab with two halo slices, its gradient, one saved slice
+    // device: the slab with two halo slices, its updated slices, one saved slice
     if (cap <= fixed || (cap - fixed) / sb < 5)
         return fail(CT_ERR_CAP, "device memory cap is below one slab slice plus halos and buffers");
     int64_t h = (int64_t)(((cap - fixed) / sb - 3) / 2);
@@ -683,7 +790,7 @@ ct_status tv_host_run(const ct_geometry &g, float *hx, int32_t nsteps, double la
     CT_HIP(CT_MALLOC(&xb.p, (size_t)(h + 2) * sb));
     CT_HIP(CT_MALLOC(&gb.p, (size_t)h * sb));
     CT_HIP(CT_MALLOC(&saved.p, (size_t)sb));
-    CT_HIP(CT_MALLOC(&parts.p, DOT_BLOCKS * 8));
+    CT_HIP(CT_MALLOC(&parts.p, 2 * DOT_BLOCKS * 8));
     CT_HIP(CT_MALLOC(&scal.p, 4 * 8));
     float *xbuf = (float *)xb.p, *gbuf = (float *)gb.p;
     double *dscal = (double *)scal.p;
@@ -694,13 +801,12 @@ ct_status tv_host_run(const ct_geometry &g, float *hx, int32_t nsteps, double la
         m0 = std::max<int64_t>(0, o0 - 1);
         m1 = std::min(nz, o1 + 1);
     };
-    auto grad = [&](int64_t m0, int64_t o0, int64_t o1) -> ct_status {
-        return launch_tv_grad((const float *)xbuf, gbuf, nx, ny, (int)nz, (float)eps, m0, o0, o1 - o0, s);
-    };
-    auto dot_host = [&](const float *a, int64_t n, double &out) -> ct_status {
-        ct_status e = dot_f64(a, a, CT_F32, n, dscal + 3, (double *)parts.p, s);
+    // ||g||^2 (and, first step, ||x||^2) of the slab's own slices
+    auto norms = [&](int64_t m0, int64_t o0, int64_t o1, bool with_x, double (&out)[3]) -> ct_status {
+        ct_status e = launch_tv_norm(xbuf, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), eps, with_x, nullptr,
+                                     (double *)parts.p, dscal, lambda, s);
         if (e != CT_OK) return e;
-        CT_HIP(hipMemcpyAsync(&out, dscal + 3, 8, hipMemcpyDeviceToHost, s));
+        CT_HIP(hipMemcpyAsync(out, dscal, sizeof(out), hipMemcpyDeviceToHost, s));
         CT_HIP(hipStreamSynchronize(s));
         return CT_OK;
     };
@@ -713,14 +819,10 @@ ct_status tv_host_run(const ct_geometry &g, float *hx, int32_t nsteps, double la
             bounds(n, o0, o1, m0, m1);
             CT_HIP(hipMemcpyAsync(xbuf, hx + m0 * slice, (size_t)(m1 - m0) * sb, hipMemcpyHostToDevice, s));
             st.bytes_h2d += (double)(m1 - m0) * sb;
-            if ((e = grad(m0, o0, o1)) != CT_OK) return e;
-            double d = 0.0;
-            if ((e = dot_host(gbuf, (o1 - o0) * slice, d)) != CT_OK) return e;
-            gg += d;
-            if (step == 0) {
-                if ((e = dot_host(xbuf + (o0 - m0) * slice, (o1 - o0) * slice, d)) != CT_OK) return e;
-                xx += d;
-            }
+            double d[3] = {0.0, 0.0, 0.0};
+            if ((e = norms(m0, o0, o1, step == 0, d)) != CT_OK) return e;
+            gg += d[2];
+            if (step == 0) xx += d[0];
         }
         if (step == 0) alpha = lambda * std::sqrt(xx);
         if (tv_verbose()) {
@@ -738,13 +840,11 @@ ct_status tv_host_run(const ct_geometry &g, float *hx, int32_t nsteps, double la
             if (n > 0) CT_HIP(hipMemcpyAsync(xbuf, saved.p, (size_t)sb, hipMemcpyDeviceToDevice, s));
             if (n + 1 < nsp)
                 CT_HIP(hipMemcpyAsync(saved.p, xbuf + (o1 - 1 - m0) * slice, (size_t)sb, hipMemcpyDeviceToDevice, s));
-            if ((e = grad(m0, o0, o1)) != CT_OK) return e;
             const int64_t nown = (o1 - o0) * slice;
-            hipLaunchKernelGGL(k_tv_update, dim3(ew_grid(nown)), dim3(EW_THREADS), 0, s, xbuf + (o0 - m0) * slice,
-                               (const float *)gbuf, (const double *)dscal, nown);
-            CT_HIP(hipGetLastError());
-            CT_HIP(hipMemcpyAsync(hx + o0 * slice, xbuf + (o0 - m0) * slice, (size_t)nown * 4, hipMemcpyDeviceToHost,
-                                  s));
+            if ((e = launch_tv_apply(xbuf, gbuf, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), eps, o0, dscal, s)) !=
+                CT_OK)
+                return e;
+            CT_HIP(hipMemcpyAsync(hx + o0 * slice, gbuf, (size_t)nown * 4, hipMemcpyDeviceToHost, s));
             CT_HIP(hipStreamSynchronize(s));
             st.bytes_d2h += (double)nown * 4;
         }
@@ -778,7 +878,7 @@ ct_status tv_host_run_halo(const ct_geometry &g, float *hx, int32_t nsteps, doub
     const int64_t slice = (int64_t)nx * ny;
     const uint64_t sb = (uint64_t)slice * sizeof(float);
     const uint64_t fixed = TV_RESERVE + align256(DOT_BLOCKS * 8) + align256(4 * 8);
-    // device: the slab with its halos, the gradient of the same, `depth` saved slices
+    // device: the slab with its halos twice (the steps alternate), `depth` saved slices
     if (cap <= fixed || (cap - fixed) / sb < (uint64_t)(5 * d + 2))
         return fail(CT_ERR_CAP, "device memory cap is below one slab slice plus halos and buffers");
     int64_t h = (int64_t)(((cap - fixed) / sb - 5 * d) / 2);
@@ -795,7 +895,7 @@ ct_status tv_host_run_halo(const ct_geometry &g, float *hx, int32_t nsteps, doub
     CT_HIP(CT_MALLOC(&xb.p, (size_t)(h + 2 * d) * sb));
     CT_HIP(CT_MALLOC(&gb.p, (size_t)(h + 2 * d) * sb));
     CT_HIP(CT_MALLOC(&saved.p, (size_t)d * sb));
-    CT_HIP(CT_MALLOC(&parts.p, DOT_BLOCKS * 8));
+    CT_HIP(CT_MALLOC(&parts.p, 2 * DOT_BLOCKS * 8));
     CT_HIP(CT_MALLOC(&scal.p, 4 * 8));
     float *xbuf = (float *)xb.p, *gbuf = (float *)gb.p, *sbuf = (float *)saved.p;
     double *dscal = (double *)scal.p;
@@ -831,22 +931,21 @@ ct_status tv_host_run_halo(const ct_geometry &g, float *hx, int32_t nsteps, doub
                                       s));
             }
             const int64_t nown = (o1 - o0) * slice;
+            float *cur = xbuf, *next = gbuf;
             for (int64_t i = 0; i < k; ++i) {
                 const int64_t r0 = m0 == 0 ? 0 : m0 + i + 1, r1 = m1 == nz ? nz : m1 - i - 1;
-                if ((e = launch_tv_grad((const float *)xbuf, gbuf, nx, ny, (int)nz, (float)eps, m0, r0, r1 - r0, s)) !=
-                    CT_OK)
-                    return e;
-                if ((e = dot_f64(gbuf + (o0 - r0) * slice, gbuf + (o0 - r0) * slice, CT_F32, nown, dscal + 2,
-                                 (double *)parts.p, s)) != CT_OK)
+                if ((e = launch_tv_norm(cur, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), eps, false, nullptr,
+                                        (double *)parts.p, dscal, lambda, s)) != CT_OK)
                     return e;
                 hipLaunchKernelGGL(k_scale_entry, dim3(1), dim3(1), 0, s, dscal + 2, (double)nz / (double)(o1 - o0));
                 CT_HIP(hipGetLastError());
-                const int64_t nr = (r1 - r0) * slice;
-                hipLaunchKernelGGL(k_tv_update, dim3(ew_grid(nr)), dim3(EW_THREADS), 0, s, xbuf + (r0 - m0) * slice,
-                                   (const float *)gbuf, (const double *)dscal, nr);
-                CT_HIP(hipGetLastError());
+                // the slices a later step still reads lie in [r0, r1)
+                if ((e = launch_tv_apply(cur, next, tv_args(nx, ny, (int)nz, eps, m0, r0, r1 - r0), eps, m0, dscal, s)) !=
+                    CT_OK)
+                    return e;
+                std::swap(cur, next);
             }
-            CT_HIP(hipMemcpyAsync(hx + o0 * slice, xbuf + (o0 - m0) * slice, (size_t)nown * 4, hipMemcpyDeviceToHost,
+            CT_HIP(hipMemcpyAsync(hx + o0 * slice, cur + (o0 - m0) * slice, (size_t)nown * 4, hipMemcpyDeviceToHost,
                                   s));
             CT_HIP(hipStreamSynchronize(s));
             st.bytes_d2h += (double)nown * 4;
