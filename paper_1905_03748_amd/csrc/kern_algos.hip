@@ -381,6 +381,14 @@ __device__ __forceinline__ float rof_div(const float *__restrict__ px, const flo
     return d;
 }
 
+// The iteration's arithmetic, shared by the one-pass and two-pass kernels (explicit FMAs, so that both
+// round alike): w from div p, the step's denominator 1 + tau |grad w|, and a component's new value.
+__device__ __forceinline__ float rof_w(float div, float f, float inv_lam) { return fmaf(-f, inv_lam, div); }
+__device__ __forceinline__ float rof_den(float gx, float gy, float gz, float tau) {
+    return fmaf(tau, sqrtf(fmaf(gz, gz, fmaf(gy, gy, gx * gx))), 1.0f);
+}
+__device__ __forceinline__ float rof_p(float p, float g, float tau, float den) { return fmaf(tau, g, p) / den; }
+
 // w = div p - f / lam
 __global__ __launch_bounds__(256) void k_rof_w(const float *__restrict__ f, const float *__restrict__ px,
                                                const float *__restrict__ py, const float *__restrict__ pz,
@@ -391,7 +399,7 @@ __global__ __launch_bounds__(256) void k_rof_w(const float *__restrict__ f, cons
     if (i >= nx || j >= ny) return;
     const int64_t sy = nx, sz = (int64_t)nx * ny;
     const int64_t o = k * sz + (int64_t)j * sy + i;
-    w[o] = rof_div(px, py, pz, i, j, k, nx, ny, nz, o, sy, sz) - f[o] * inv_lam;
+    w[o] = rof_w(rof_div(px, py, pz, i, j, k, nx, ny, nz, o, sy, sz), f[o], inv_lam);
 }
 
 // p <- (p + tau grad w) / (1 + tau |grad w|), forward differences, zero at the last index
@@ -408,10 +416,93 @@ __global__ __launch_bounds__(256) void k_rof_p(const float *__restrict__ w, floa
     const float gx = i < nx - 1 ? w[o + 1] - wc : 0.0f;
     const float gy = j < ny - 1 ? w[o + sy] - wc : 0.0f;
     const float gz = k < nz - 1 ? w[o + sz] - wc : 0.0f;
-    const float den = 1.0f + tau * sqrtf(gx * gx + gy * gy + gz * gz);
-    px[o] = (px[o] + tau * gx) / den;
-    py[o] = (py[o] + tau * gy) / den;
-    pz[o] = (pz[o] + tau * gz) / den;
+    const float den = rof_den(gx, gy, gz, tau);
+    px[o] = rof_p(px[o], gx, tau, den);
+    py[o] = rof_p(py[o], gy, tau, den);
+    pz[o] = rof_p(pz[o], gz, tau, den);
+}
+
+// One whole iteration, p into q (another dual field; a voxel's step reads its neighbours' old p), without
+// storing w: 28 bytes of memory traffic per voxel where the two passes take 48.  A thread walks a run of
+// slices of its (i, j) column and needs w at the voxel, at its right neighbour, at the row above and at
+// the slice above.  w of the slice above becomes the next slice's own; the right neighbour's comes from
+// the next lane (the last lane forms it itself); the row above's is formed again (its loads are the next
+// wave's, in L1).  So a slice takes 11 loads (4.7 address-unit cycles each, a quarter of the time its
+// 28 bytes take from HBM) and no LDS or barrier.  FIRST: p = 0 is not read.  The arithmetic is that of the
+// two passes, bit for bit.  Bound: HBM.  512^3, 10 iterations 20.1 -> 10.7 ms (3.8 TB/s of the 28 bytes);
+// 301 x 277 x 193, 20 iterations 4.87 -> 3.04 ms.
+constexpr int ROF_TY = 4;
+struct RofArgs {
+    const float *f, *px, *py, *pz;
+    float *qx, *qy, *qz;
+    int nx, ny, nz, zr;
+    float inv_lam, tau;
+};
+template <bool FIRST>
+__global__ __launch_bounds__(64 * ROF_TY) void k_rof_step(RofArgs A) {
+    const int lane = threadIdx.x & 63;
+    const int iu = blockIdx.x * 64 + lane, i = min(iu, A.nx - 1);  // lanes past the row repeat its last voxel
+    const int j = blockIdx.y * ROF_TY + (threadIdx.x >> 6);
+    if (j >= A.ny) return;
+    const int64_t sy = A.nx, sz = (int64_t)A.nx * A.ny;
+    const int k0 = blockIdx.z * A.zr, k1 = min(k0 + A.zr, A.nz);
+    const bool hx = i < A.nx - 1, hy = j < A.ny - 1, lx = i > 0, ly = j > 0;
+    const int64_t ow = lx ? -1 : 0, os = ly ? -sy : 0, on = hy ? sy : 0, oe = hx ? 1 : 0;
+    // w at offset o whose x, y and z components of p are (x, y, z) there and (xm, ym, zm) one voxel below
+    // along each axis; h / l: it is not the last / first voxel of the axis
+    auto w_of = [&](float f, float x, float xm, bool h_x, bool l_x, float y, float ym, bool h_y, bool l_y, float z,
+                    float zm, bool h_z, bool l_z) {
+        float d = (h_z ? z : 0.0f) - (l_z ? zm : 0.0f);
+        d += (h_y ? y : 0.0f) - (l_y ? ym : 0.0f);
+        d += (h_x ? x : 0.0f) - (l_x ? xm : 0.0f);
+        return rof_w(d, f, A.inv_lam);
+    };
+    auto ld = [&](const float *a, int64_t o) { return FIRST ? 0.0f : a[o]; };
+    int64_t o = (int64_t)k0 * sz + (int64_t)j * sy + i;
+    const int64_t od = k0 > 0 ? -sz : 0;
+    const bool edge = lane == 63 && hx;  // forms its right neighbour's w itself
+    const bool hx2 = i + 1 < A.nx - 1, hy2 = j + 1 < A.ny - 1;
+    // the slice's own p, and p_z of the slice below at the row above and (last lane) at the right neighbour
+    float x = ld(A.px, o), y = ld(A.py, o), z = ld(A.pz, o);
+    float w = w_of(A.f[o], x, ld(A.px, o + ow), hx, lx, y, ld(A.py, o + os), hy, ly, z, ld(A.pz, o + od),
+                   k0 < A.nz - 1, k0 > 0);
+    float znm = ld(A.pz, o + on + od), zem = edge ? ld(A.pz, o + oe + od) : 0.0f;
+    for (int k = k0; k < k1; ++k, o += sz) {
+        const bool hz = k < A.nz - 1, lz = k > 0;
+        // the slice above
+        float xu = 0.0f, yu = 0.0f, zu = 0.0f, wu = 0.0f;
+        if (hz) {
+            const int64_t u = o + sz;
+            xu = ld(A.px, u);
+            yu = ld(A.py, u);
+            zu = ld(A.pz, u);
+            wu = w_of(A.f[u], xu, ld(A.px, u + ow), hx, lx, yu, ld(A.py, u + os), hy, ly, zu, z, k + 1 < A.nz - 1, true);
+        }
+        // the row above
+        const int64_t n = o + on;
+        const float zn = ld(A.pz, n);
+        const float wn = w_of(A.f[n], ld(A.px, n), ld(A.px, n + ow), hx, lx, ld(A.py, n), y, hy2, true, zn, znm, hz, lz);
+        znm = zn;
+        // the right neighbour
+        float we = __shfl_down(w, 1, 64);
+        if (edge) {
+            const int64_t e = o + oe;
+            const float ze = ld(A.pz, e);
+            we = w_of(A.f[e], ld(A.px, e), x, hx2, true, ld(A.py, e), ld(A.py, e + os), hy, ly, ze, zem, hz, lz);
+            zem = ze;
+        }
+        const float gx = hx ? we - w : 0.0f, gy = hy ? wn - w : 0.0f, gz = hz ? wu - w : 0.0f;
+        const float den = rof_den(gx, gy, gz, A.tau);
+        if (iu < A.nx) {
+            A.qx[o] = rof_p(x, gx, A.tau, den);
+            A.qy[o] = rof_p(y, gy, A.tau, den);
+            A.qz[o] = rof_p(z, gz, A.tau, den);
+        }
+        x = xu;
+        y = yu;
+        z = zu;
+        w = wu;
+    }
 }
 
 // u = f - lam div p, in place over f (each voxel reads only its own f)
@@ -448,8 +539,8 @@ struct Workspace {
             base = (char *)user;
             return CT_OK;
         }
-        owned = true;
         CT_HIP(CT_MALLOC_ASYNC((void **)&base, bytes ? bytes : 256, s));
+        owned = true;
         return CT_OK;
     }
     ~Workspace() {
@@ -690,33 +781,67 @@ ct_status tv_run(const ct_geometry &g, void *xs, ct_dtype vt, int32_t nsteps, do
 
 
 // ---------------------------------------------------------------------------------------------
-// ROF model (Chambolle's projection): workspace px, py, pz, w
+// ROF model (Chambolle's projection)
 
-size_t rof_workspace(const ct_geometry &g) {
-    const size_t nv = (size_t)g.nVoxel[0] * g.nVoxel[1] * g.nVoxel[2];
-    return 4 * align256(nv * 4);
+namespace {
+// Whether an iteration runs in one pass between two dual fields (workspace: six volumes) or in two
+// passes over one (four: px, py, pz, w).  The one-pass form takes half the time; above 16 GiB per volume
+// its two more volumes would be what no longer fits a 288 GB device, so the four-volume form stays there,
+// and where the library's own allocation of six fails.
+bool rof_one_pass(const ct_geometry &g) {
+    return (uint64_t)g.nVoxel[0] * g.nVoxel[1] * g.nVoxel[2] <= (uint64_t(4) << 30);
 }
+size_t rof_volumes(const ct_geometry &g, int n) {
+    return (size_t)n * align256((size_t)g.nVoxel[0] * g.nVoxel[1] * g.nVoxel[2] * 4);
+}
+}  // namespace
+
+size_t rof_workspace(const ct_geometry &g) { return rof_volumes(g, rof_one_pass(g) ? 6 : 4); }
 
 ct_status rof_run(const ct_geometry &g, void *x, int32_t niter, double lambda, double tau, void *work, hipStream_t st) {
     const int nx = (int)g.nVoxel[0], ny = (int)g.nVoxel[1], nz = (int)g.nVoxel[2];
     const int64_t nv = (int64_t)nx * ny * nz;
+    if (niter == 0) return CT_OK;  // u = f
+    bool one = rof_one_pass(g);
     Workspace ws;
     ct_status s = ws.acquire(work, rof_workspace(g), st);
-    if (s != CT_OK) return s;
-    float *px = (float *)ws.take(nv * 4), *py = (float *)ws.take(nv * 4), *pz = (float *)ws.take(nv * 4);
-    float *w = (float *)ws.take(nv * 4);
-    hipLaunchKernelGGL(k_fill_zero, dim3(ew_grid(nv)), dim3(EW_THREADS), 0, st, px, nv);
-    hipLaunchKernelGGL(k_fill_zero, dim3(ew_grid(nv)), dim3(EW_THREADS), 0, st, py, nv);
-    hipLaunchKernelGGL(k_fill_zero, dim3(ew_grid(nv)), dim3(EW_THREADS), 0, st, pz, nv);
-    CT_HIP(hipGetLastError());
-    const dim3 grid((nx + 63) / 64, (ny + 3) / 4, nz);
-    for (int32_t it = 0; it < niter; ++it) {
-        hipLaunchKernelGGL(k_rof_w, grid, dim3(256), 0, st, (const float *)x, px, py, pz, w, nx, ny, nz,
-                           (float)(1.0 / lambda));
-        hipLaunchKernelGGL(k_rof_p, grid, dim3(256), 0, st, (const float *)w, px, py, pz, nx, ny, nz, (float)tau);
-        CT_HIP(hipGetLastError());
+    if (s == CT_ERR_OOM && one) {
+        (void)hipGetLastError();
+        one = false;
+        s = ws.acquire(nullptr, rof_volumes(g, 4), st);
     }
-    hipLaunchKernelGGL(k_rof_u, grid, dim3(256), 0, st, (float *)x, px, py, pz, nx, ny, nz, (float)lambda);
+    if (s != CT_OK) return s;
+    float *p[3], *q[3];
+    for (auto &v : p) v = (float *)ws.take(nv * 4);
+    const dim3 grid((nx + 63) / 64, (ny + 3) / 4, nz);
+    if (one) {
+        for (auto &v : q) v = (float *)ws.take(nv * 4);
+        // runs of 8 slices, 4 where those would leave fewer than 2048 blocks of 4 waves (longer ones read
+        // less twice but keep fewer rows of one slice in flight: 301 x 277 x 193, 20 iterations, runs of
+        // 8 / 16 / 32 slices 3.04 / 3.14 / 3.35 ms; 512^3, 10 iterations, 10.70 / 10.83 / 10.84 ms)
+        const int zr = (int64_t)grid.x * grid.y * ((nz + 7) / 8) < 2048 ? 4 : 8;
+        const dim3 rgrid(grid.x, (ny + ROF_TY - 1) / ROF_TY, (nz + zr - 1) / zr);
+        for (int32_t it = 0; it < niter; ++it) {
+            const RofArgs A{(const float *)x, p[0], p[1], p[2], q[0], q[1], q[2], nx, ny, nz, zr,
+                            (float)(1.0 / lambda), (float)tau};
+            if (it == 0) hipLaunchKernelGGL((k_rof_step<true>), rgrid, dim3(64 * ROF_TY), 0, st, A);
+            else hipLaunchKernelGGL((k_rof_step<false>), rgrid, dim3(64 * ROF_TY), 0, st, A);
+            CT_HIP(hipGetLastError());
+            std::swap(p, q);
+        }
+    } else {
+        float *w = (float *)ws.take(nv * 4);
+        for (auto &v : p) hipLaunchKernelGGL(k_fill_zero, dim3(ew_grid(nv)), dim3(EW_THREADS), 0, st, v, nv);
+        CT_HIP(hipGetLastError());
+        for (int32_t it = 0; it < niter; ++it) {
+            hipLaunchKernelGGL(k_rof_w, grid, dim3(256), 0, st, (const float *)x, p[0], p[1], p[2], w, nx, ny, nz,
+                               (float)(1.0 / lambda));
+            hipLaunchKernelGGL(k_rof_p, grid, dim3(256), 0, st, (const float *)w, p[0], p[1], p[2], nx, ny, nz,
+                               (float)tau);
+            CT_HIP(hipGetLastError());
+        }
+    }
+    hipLaunchKernelGGL(k_rof_u, grid, dim3(256), 0, st, (float *)x, p[0], p[1], p[2], nx, ny, nz, (float)lambda);
     CT_HIP(hipGetLastError());
     return CT_OK;
 }
