@@ -114,7 +114,7 @@ inline Slab full_slab(const ct_geometry &g) {
 // angles [a0, a1) starting at projection 0).
 // vcopy: optional copy of vol in the layout the projector reads, kept by the caller (then no
 // scratch copy is made): for Siddon the column-major slots of launch_zcols (for a slab launch:
-// its mem_n slices, mem_n + 2 slots per column), for the interpolated projector the [z][x][y]
+// its mem_n slices, mem_n + 2 slots per column; with the guard elements of zcol_base), for the interpolated projector the [z][x][y]
 // transpose of launch_transpose_xy.
 ct_status launch_forward(ct_plan *p, ct_projector kind, const void *vol, ct_dtype vt, void *proj,
                          ct_dtype pt, int accumulate, int64_t a0, int64_t a1, const Slab &slab,
@@ -140,6 +140,12 @@ ct_status launch_zcols_inv_piece(const void *vz, ct_dtype vt, void *dst, int64_t
 // the exact adjoint runs its column kernel (which supports column-major slabs) for this geometry
 bool adj_col_ok(const ct_plan *p);
 inline int64_t zcol_elems(const ct_geometry &g) { return g.nVoxel[0] * g.nVoxel[1] * (g.nVoxel[2] + 2); }
+// The column walk reads past a column's ends, into its neighbours' pads; a copy therefore has ZCOL_GUARD
+// elements before its first column and after its last (launch_zcols zeroes those that are used).
+// zcol_bytes: a resident copy with its guards, zcol_base: where its first column starts.
+constexpr int ZCOL_GUARD = 4;
+inline size_t zcol_bytes(const ct_geometry &g, size_t esize) { return (size_t)(zcol_elems(g) + 2 * ZCOL_GUARD) * esize; }
+inline void *zcol_base(void *p, size_t esize) { return (char *)p + ZCOL_GUARD * esize; }
 // whether the column Siddon walk is valid for angles [a0, a1) of the plan
 bool zcol_ok(const ct_plan *p, int64_t a0, int64_t a1);
 // adj_scratch (optional, adj_bytes): device memory for the exact adjoint's transposed projection

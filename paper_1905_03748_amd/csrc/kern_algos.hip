@@ -591,7 +591,7 @@ size_t cgls_workspace(const ct_plan *p, ct_dtype, ct_dtype) {
     const size_t nv = (size_t)g.nVoxel[0] * g.nVoxel[1] * g.nVoxel[2];
     const size_t np = (size_t)g.nDetector[0] * g.nDetector[1] * p->angles.size();
     return 2 * align256(nv * 4) + 2 * align256(np * 4) + align256(DOT_BLOCKS * 8) + align256(S_COUNT * 8) +
-           align256((size_t)zcol_elems(g) * 4) + align256(p->angles.size() * adj_chunk_bytes_per_angle(g));
+           align256(zcol_bytes(g, 4)) + align256(p->angles.size() * adj_chunk_bytes_per_angle(g));
 }
 
 ct_status cgls_run(ct_plan *p, const void *b, ct_dtype pt, void *x, ct_dtype vt, int32_t niter, double *resid,
@@ -609,7 +609,7 @@ ct_status cgls_run(ct_plan *p, const void *b, ct_dtype pt, void *x, ct_dtype vt,
     float *pv = (float *)ws.take(nv * 4);
     double *parts = (double *)ws.take(DOT_BLOCKS * 8);
     double *scal = (double *)ws.take(S_COUNT * 8);
-    void *vz = ws.take((size_t)zcol_elems(g) * 4);
+    void *vz = zcol_base(ws.take(zcol_bytes(g, 4)), 4);
     const size_t qbytes = (size_t)na * adj_chunk_bytes_per_angle(g);
     void *yq = ws.take(qbytes);
     const Slab full = full_slab(g);
@@ -671,7 +671,7 @@ size_t sart_workspace(const ct_plan *p, int32_t block) {
     const ct_geometry &g = p->g;
     const size_t pix = (size_t)g.nDetector[0] * g.nDetector[1];
     const size_t nb = (size_t)std::max<int32_t>(block, 1);
-    return align256(pix * p->angles.size() * 4) + 2 * align256(pix * nb * 4) + align256((size_t)zcol_elems(g) * 4);
+    return align256(pix * p->angles.size() * 4) + 2 * align256(pix * nb * 4) + align256(zcol_bytes(g, 4));
 }
 
 // OS-SART: the angles in natural order, cut into consecutive subsets of `block` (the last one may be
@@ -690,7 +690,7 @@ ct_status sart_run(ct_plan *p, const void *b, ct_dtype pt, void *x, ct_dtype vt,
     float *chord = (float *)ws.take(pix * na * 4);
     float *r = (float *)ws.take(pix * block * 4);
     float *rT = (float *)ws.take(pix * block * 4);
-    float *xz = (float *)ws.take((size_t)zcol_elems(g) * 4);
+    float *xz = (float *)zcol_base(ws.take(zcol_bytes(g, 4)), 4);
     const float thr = (float)(1e-2 * std::fmin(g.dVoxel[0], std::fmin(g.dVoxel[1], g.dVoxel[2])));
     const int nu = (int)g.nDetector[0], nv = (int)g.nDetector[1];
     CK(launch_ray_chord(p, chord, 0, na, st));

@@ -278,9 +278,6 @@ __global__ __launch_bounds__(FWD_TU * FWD_TV) void k_siddon(const TV *__restrict
 #ifndef CT_ZC_COLS
 #define CT_ZC_COLS 4
 #endif
-#ifndef CT_ZC_ORDER
-#define CT_ZC_ORDER 3
-#endif
 #ifndef CT_ZC_AK
 #define CT_ZC_AK 32
 #endif
@@ -357,10 +354,51 @@ struct XQuad<bf16s> {
     }
 };
 
+// Four consecutive slots of a column in one load (16 bytes for FP32, 8 for the 16-bit types).
+template <typename TV>
+__device__ __forceinline__ void zquad(const TV *p, float (&q)[4]);
+template <>
+__device__ __forceinline__ void zquad<float>(const float *p, float (&q)[4]) {
+    XQuad<float>::ld(p, q[0], q[1], q[2], q[3]);
+}
+template <>
+__device__ __forceinline__ void zquad<f16s>(const f16s *p, float (&q)[4]) {
+    XQuad<f16s>::ld(p, q[0], q[1], q[2], q[3]);
+}
+template <>
+__device__ __forceinline__ void zquad<bf16s>(const bf16s *p, float (&q)[4]) {
+    XQuad<bf16s>::ld(p, q[0], q[1], q[2], q[3]);
+}
+
 #ifndef CT_ZC_BATCH
 #define CT_ZC_BATCH 8
 #endif
 constexpr int ZC_B = CT_ZC_BATCH;  // xy pieces per trip
+
+// Column group, angle and row group of a block.
+__device__ __forceinline__ void col_block(const FwdArgs &A, int &cb, int &ai, int &rg) {
+    int bid = blockIdx.x;
+    // workgroups are dealt to the 8 XCDs in turn: give each XCD CT_ZC_XCD_W consecutive column
+    // groups out of every 8 * CT_ZC_XCD_W, so rays that share voxels share an L2
+    {
+        constexpr int W = CT_ZC_XCD_W, C = 8 * W;
+        const int full = (int)(gridDim.x / C) * C;
+        if (bid < full) bid = (bid / C) * C + (bid % 8) * W + (bid % C) / 8;
+    }
+    // groups of CT_ZC_AK consecutive angles: angle within the group fastest, then column block
+    constexpr int AK = CT_ZC_AK;
+    const int per = A.nang * A.cblocks, idx = bid % per, full = A.nang / AK;
+    rg = bid / per;
+    if (idx < full * AK * A.cblocks) {
+        const int r = idx % (AK * A.cblocks);
+        cb = r / AK;
+        ai = (idx / (AK * A.cblocks)) * AK + r % AK;
+    } else {
+        const int rem = A.nang - full * AK, i2 = idx - full * AK * A.cblocks;
+        cb = i2 / rem;
+        ai = full * AK + i2 % rem;
+    }
+}
 
 // Per-row state of the column walk.
 template <int ROWS>
@@ -451,46 +489,8 @@ __global__ __launch_bounds__(64 * ZC_COLS) void k_siddon_col(const TV *__restric
                                                              FwdArgs A) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
-    int bid = blockIdx.x;
-#if CT_ZC_XCD_W > 1
-    // workgroups are dealt to the 8 XCDs in turn: give each XCD CT_ZC_XCD_W consecutive column
-    // groups out of every 8 * CT_ZC_XCD_W, so rays that share voxels share an L2
-    {
-        constexpr int W = CT_ZC_XCD_W, C = 8 * W;
-        const int full = (int)(gridDim.x / C) * C;
-        if (bid < full) bid = (bid / C) * C + (bid % 8) * W + (bid % C) / 8;
-    }
-#endif
     int cb, ai, rg;
-#if CT_ZC_ORDER == 1
-    ai = bid % A.nang;
-    cb = (bid / A.nang) % A.cblocks;
-    rg = bid / A.nang / A.cblocks;
-#elif CT_ZC_ORDER == 2
-    cb = bid % A.cblocks;
-    rg = (bid / A.cblocks) % A.rgroups;
-    ai = bid / A.cblocks / A.rgroups;
-#elif CT_ZC_ORDER == 3
-    {
-        // groups of CT_ZC_AK consecutive angles: angle within the group fastest, then column block
-        constexpr int AK = CT_ZC_AK;
-        const int per = A.nang * A.cblocks, idx = bid % per, full = A.nang / AK;
-        rg = bid / per;
-        if (idx < full * AK * A.cblocks) {
-            const int r = idx % (AK * A.cblocks);
-            cb = r / AK;
-            ai = (idx / (AK * A.cblocks)) * AK + r % AK;
-        } else {
-            const int rem = A.nang - full * AK, i2 = idx - full * AK * A.cblocks;
-            cb = i2 / rem;
-            ai = full * AK + i2 % rem;
-        }
-    }
-#else
-    cb = bid % A.cblocks;
-    ai = (bid / A.cblocks) % A.nang;
-    rg = bid / A.cblocks / A.nang;
-#endif
+    col_block(A, cb, ai, rg);
     const int a = cb * ZC_COLS + wave;
     if (a >= A.nu) return;
     const AngleGeo &G = A.tab[A.a0 + ai];
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(64 * ZC_COLS) void k_siddon_col(const TV *__restric
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) acc[r] = 0.0f;
     const int brow = rg * (64 * ROWS) + lane;
-    double L[ROWS];
+    double L[ROWS], iz[ROWS];  // iz: 1 / Dz, one division for the z window and the crossings
     ZRows<ROWS> Z;
     bool all_up = true, all_down = true;
     // the wave walks only where one of its rows is inside the owned slices: [t0, t1] shrinks to
@@ -536,6 +536,7 @@ __global__ __launch_bounds__(64 * ZC_COLS) void k_siddon_col(const TV *__restric
         double win0 = 1e300, win1 = -1e300;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
+            iz[r] = 0.0;
             const int b = min(brow + 64 * r, A.nv - 1);
             const double Dz = ((b - A.cv) * A.dv + A.offv) / A.dz;
             if (fabs(Dz * A.dz) < 1e-12 * Lref) {
@@ -544,7 +545,8 @@ __global__ __launch_bounds__(64 * ZC_COLS) void k_siddon_col(const TV *__restric
                     win1 = fmax(win1, t1);
                 }
             } else {
-                const double ta = (zlo - G.S[2]) / Dz, tb = (zhi - G.S[2]) / Dz;
+                iz[r] = 1.0 / Dz;
+                const double ta = (zlo - G.S[2]) * iz[r], tb = (zhi - G.S[2]) * iz[r];
                 win0 = fmin(win0, fmin(ta, tb));
                 win1 = fmax(win1, fmax(ta, tb));
             }
@@ -587,8 +589,8 @@ __global__ __launch_bounds__(64 * ZC_COLS) void k_siddon_col(const TV *__restric
             Z.inv[r] = 0.0f;
             Z.c1[r] = (lo + 1.0f > (float)zr) ? FLT_MAX : -FLT_MAX;
         } else {
-            Z.inv[r] = (float)(1.0 / Dz);
-            Z.c1[r] = (float)((1.0 - zr) / Dz);
+            Z.inv[r] = (float)iz[r];
+            Z.c1[r] = (float)((1.0 - zr) * iz[r]);
         }
         all_up = all_up && Z.up[r];
         all_down = all_down && !Z.up[r];
@@ -643,8 +645,335 @@ __global__ __launch_bounds__(64 * ZC_COLS) void k_siddon_col(const TV *__restric
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// Column Siddon, two neighbouring rows per lane.
+//
+// The walk of k_siddon_col is bound by the texture-address unit, which takes 16 cycles for a load of 8
+// bytes per lane and no more for one of 16.  So a lane takes rows 2l and 2l + 1 of its wave's 128 and
+// serves both from one load of four slots.  At the ray parameter t the upper row lies delta = t dv / dz
+// slots above the lower one, the same for all lanes; with D = floor(delta) (0 or 1; the host checks
+// delta < 2) the lower row meets slots lo and lo + 1 of the four and the upper one two of lo + D .. lo +
+// D + 2.  Which two follows from its crossing time T1 of plane lo + D + 1 alone: if that does not lie
+// ahead at the piece's start (for a falling row: at its end), the row is one slot higher for the whole
+// piece.  The walk runs with D = 0 up to delta = 1 and with D = 1 from there; the piece that holds the
+// change is walked once on each side of it.
+//
+// The xy path is the same for the whole wave, so the lanes form it together, 64 pieces at a time: lane l
+// finds by the merge path how many x and y planes the first p0 + l crossings hold, which gives its
+// piece's end and column; the loop reads them back lane by lane into scalar registers (two instructions
+// per piece where stepping took about ten).  The crossing times are those of k_siddon_col, so the pieces
+// are the same, except that a crossing of an x and a y plane at the same time is two, one of them empty.
+//
+// Every lane's slots lie in [-1, nz + 3] of its column: -1 and nz + 2 are the zero pads of the columns
+// before and after (for the first and last column the copy's guard elements), nz + 3 is loaded where lo =
+// nz and taken as zero.
+//
+// Bound: the address unit (82 % busy, 20 cycles per load) and VALU issue (28 instructions per load of two
+// rows) about evenly, with 124 GB per launch past L2 (6 TB/s) at 512^3 / 360 angles: 26.9 -> 20.9 ms there
+// (2.3e12 voxel projections per second), 243 x 251 x 187 / 175 angles of 301 x 233 1.86 -> 1.56 ms.
+#ifndef CT_ZP_BATCH
+#define CT_ZP_BATCH 8
+#endif
+constexpr int ZP_B = CT_ZP_BATCH;  // xy pieces per trip (8 / 4 at 512^3: 20.8 / 24.0 ms)
+#ifndef CT_ZP_WAVES
+#define CT_ZP_WAVES 4
+#endif
+
+// Per-lane state of the two rows; slots are relative to the lower row's entry slot k0.
+struct ZPairRows {
+    float Zr, Dz, inv, c1;  // lower row: z = Zr + t Dz; plane lo + 1 is crossed at lo inv + c1
+    float inv2, c2;         // upper row: plane lo + 1 is crossed at lo inv2 + c2
+    float lmin, lmax;       // lo is kept in [lmin, lmax] (slots -1 and nz)
+    uint32_t kb;            // byte offset of slot k0, from one slot below the column
+    bool up, up2;           // rising (parallel rows count as rising)
+};
+
+// ZP_B pieces: their ends tb[u] and columns col[u] (scalar), the first one's start ta.  ORI: +1 both rows of
+// every lane rise, -1 all fall, 0 mixed.  CLAMP: some row of the wave leaves the grid in z.
+template <int ORI, int D, bool CLAMP, typename TV>
+__device__ __forceinline__ void zp_trip(const TV *__restrict__ vz, int64_t nzp, const int (&col)[ZP_B],
+                                        const float (&tb)[ZP_B], float ta, const ZPairRows &Z, float &acc0, float &acc1) {
+    float q[ZP_B][4], a0[ZP_B], a1[ZP_B], b0[ZP_B], b1[ZP_B];
+    bool hi[ZP_B], top[ZP_B];
+    float fz = floorf(fmaf(ta, Z.Dz, Z.Zr));
+    const float c2 = D == 0 ? Z.c2 : Z.c2 + Z.inv2;  // plane lo + D + 1
+    const float c3 = c2 + Z.inv2;                    // plane lo + D + 2
+#pragma unroll
+    for (int u = 0; u < ZP_B; ++u) {
+        const float fb = floorf(fmaf(tb[u], Z.Dz, Z.Zr));
+        float lo = ORI > 0 ? fz : (ORI < 0 ? fb : fminf(fz, fb));
+        if (CLAMP) lo = __builtin_amdgcn_fmed3f(lo, Z.lmin, Z.lmax);
+        fz = fb;
+        const uint32_t k = (uint32_t)((int)lo * (int)sizeof(TV)) + Z.kb;
+        zquad<TV>((const TV *)((const char *)(vz + (int64_t)col[u] * nzp - 1) + k), q[u]);
+        top[u] = CLAMP && D == 1 && lo >= Z.lmax;
+        // the lower row meets lo on one side of m and lo + 1 on the other
+        const float m = __builtin_amdgcn_fmed3f(fmaf(lo, Z.inv, Z.c1), ta, tb[u]);
+        a0[u] = m - ta;
+        a1[u] = tb[u] - m;
+        const float T1 = fmaf(lo, Z.inv2, c2), T2 = fmaf(lo, Z.inv2, c3);
+        hi[u] = ORI > 0 ? T1 <= ta : (ORI < 0 ? T1 >= tb[u] : (Z.up2 ? T1 <= ta : T1 >= tb[u]));
+        const float m2 = __builtin_amdgcn_fmed3f(hi[u] ? T2 : T1, ta, tb[u]);
+        b0[u] = m2 - ta;
+        b1[u] = tb[u] - m2;
+        ta = tb[u];
+    }
+#pragma unroll
+    for (int u = 0; u < ZP_B; ++u) {
+        const float q3 = CLAMP && D == 1 && top[u] ? 0.0f : q[u][3];
+        const float va = hi[u] ? q[u][D + 1] : q[u][D], vb = hi[u] ? (D == 0 ? q[u][2] : q3) : q[u][D + 1];
+        // rising rows meet the lower slot first, falling rows the upper one
+        const bool up = ORI > 0 || (ORI == 0 && Z.up), up2 = ORI > 0 || (ORI == 0 && Z.up2);
+        acc0 = fmaf(a0[u], up ? q[u][0] : q[u][1], acc0);
+        acc0 = fmaf(a1[u], up ? q[u][1] : q[u][0], acc0);
+        acc1 = fmaf(b0[u], up2 ? va : vb, acc1);
+        acc1 = fmaf(b1[u], up2 ? vb : va, acc1);
+    }
+}
+
+// The shared xy path: crossing i of an x plane at fma(i, dt[0], t0[0]), of a y plane likewise; it starts in
+// column (idx[0], idx[1]), steps by sg[] and ends at Te.  delta reaches 1 at ts.
+struct ZPath {
+    float t0[2], dt[2], Te, ts;
+    int idx[2], sg[2], nx;
+    int maxp;  // more pieces than the path has
+};
+
+template <int ORI, bool CLAMP, typename TV>
+__device__ __forceinline__ void zp_walk(const TV *__restrict__ vz, int64_t nzp, const ZPath &P, const ZPairRows &Z,
+                                        float &acc0, float &acc1) {
+    const int lane = threadIdx.x & 63;
+    auto X = [&](int i) { return fmaf((float)i, P.dt[0], P.t0[0]); };
+    auto Y = [&](int j) { return fmaf((float)j, P.dt[1], P.t0[1]); };
+    const float Te = P.Te;
+    float ta = 0.0f;
+    for (int p0 = 0; p0 < P.maxp; p0 += 64) {
+        // lane l: piece p = p0 + l, which follows i x crossings and p - i y crossings; i is the least for
+        // which the last y crossing comes before the next x crossing (x first where they are equal)
+        const int p = p0 + lane;
+        int i;
+        {
+            const float est = (fmaf((float)(p - 1), P.dt[1], P.t0[1]) - P.t0[0]) / (P.dt[0] + P.dt[1]);
+            i = (int)fminf(fmaxf(ceilf(est), 0.0f), (float)p);
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+                if (i > 0 && X(i - 1) > Y(p - i)) --i;
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+                if (i < p && !(X(i) > Y(p - i - 1))) ++i;
+        }
+        const int j = p - i;
+        const float s = fmaxf(i > 0 ? X(i - 1) : 0.0f, j > 0 ? Y(j - 1) : 0.0f);
+        const float e = fminf(fminf(X(i), Y(j)), Te);
+        // An empty piece weighs zero but is read, and zero times a voxel that is not finite is not zero: so
+        // it reads a column that the ray is in there.  After an x crossing that a y crossing shares: the
+        // column before; past the end of the path: the last one.
+        const int ic = s < e || i == 0 ? i : i - 1;
+        int c = (P.idx[1] + P.sg[1] * j) * P.nx + P.idx[0] + P.sg[0] * ic;
+        const unsigned long long on = __ballot(s < Te);
+        if (on != ~0ull) {
+            const int last = __builtin_amdgcn_readlane(c, max(__popcll(on) - 1, 0));
+            if (!(s < Te)) c = on ? last : P.idx[1] * P.nx + P.idx[0];
+        }
+        // the same for the pieces of the trip that holds delta = 1 and that lie on its other side
+        int cnear = c, cfar = c;
+        const int nb = __popcll(__ballot(s < P.ts));
+        if (nb > 0) {
+            const int at = __builtin_amdgcn_readlane(c, nb - 1);
+            if (!(s < P.ts)) cnear = at;
+            if (e <= P.ts) cfar = at;
+        }
+        for (int t = 0; t < 64; t += ZP_B) {
+            const float end = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e), t + ZP_B - 1));
+            int col[ZP_B];
+            float tb[ZP_B];
+            if (ta < P.ts) {
+                const float ec = fminf(e, P.ts);
+#pragma unroll
+                for (int u = 0; u < ZP_B; ++u) col[u] = __builtin_amdgcn_readlane(cnear, t + u);
+#pragma unroll
+                for (int u = 0; u < ZP_B; ++u) tb[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ec), t + u));
+                zp_trip<ORI, 0, CLAMP>(vz, nzp, col, tb, ta, Z, acc0, acc1);
+                ta = tb[ZP_B - 1];
+            }
+            if (end > P.ts) {
+                const float ec = fmaxf(e, P.ts);
+#pragma unroll
+                for (int u = 0; u < ZP_B; ++u) col[u] = __builtin_amdgcn_readlane(cfar, t + u);
+#pragma unroll
+                for (int u = 0; u < ZP_B; ++u) tb[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ec), t + u));
+                zp_trip<ORI, 1, CLAMP>(vz, nzp, col, tb, fmaxf(ta, P.ts), Z, acc0, acc1);
+                ta = end;
+            }
+            if (!(end < Te)) return;
+        }
+    }
+}
+
+// Blocks of consecutive workgroups on one XCD, and groups of CT_ZC_AK consecutive angles per column block
+// (as k_siddon_col).
+template <typename TV, typename TP>
+__global__ __launch_bounds__(64 * ZC_COLS) __attribute__((amdgpu_waves_per_eu(CT_ZP_WAVES))) void k_siddon_pair(
+    const TV *__restrict__ vz, TP *__restrict__ proj, FwdArgs A) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    int cb, ai, rg;
+    col_block(A, cb, ai, rg);
+    const int a = cb * ZC_COLS + wave;
+    if (a >= A.nu) return;
+    const AngleGeo &G = A.tab[A.a0 + ai];
+    const int nzc = A.mem_n;
+    const int64_t nzp = (int64_t)nzc + 2;
+
+    // shared xy line of the column, clipped to the grid's xy box (FP64)
+    const double ua = (a - A.cu) * A.du + A.offu;
+    const double D[2] = {G.Dc[0] + ua * G.eu[0], G.Dc[1] + ua * G.eu[1]};
+    const double mx = D[0] * A.dx, my = D[1] * A.dy;
+    const double Lxy2 = mx * mx + my * my;
+    const double Lref = sqrt(Lxy2);
+    const double hi2[2] = {A.nx - 0.5, A.ny - 0.5};
+    bool par[2];
+    double inv[2];
+    double t0 = 0.0, t1 = 1.0;
+    bool hit = true;
+#pragma unroll
+    for (int ax = 0; ax < 2; ++ax) {
+        par[ax] = fabs(ax == 0 ? mx : my) < 1e-12 * Lref;
+        inv[ax] = 0.0;
+        if (par[ax]) {
+            if (G.S[ax] < -0.5 || G.S[ax] > hi2[ax]) hit = false;
+        } else {
+            const double ta = (-0.5 - G.S[ax]) / D[ax];
+            const double tb = (hi2[ax] - G.S[ax]) / D[ax];
+            inv[ax] = 1.0 / fabs(D[ax]);
+            t0 = fmax(t0, fmin(ta, tb));
+            t1 = fmin(t1, fmax(ta, tb));
+        }
+    }
+    hit = hit && t0 < t1;
+
+    // the lane's rows b and b + 1; lanes past the last pair repeat it, and the row after the last one (odd
+    // counts) is set up like any other; their results are not stored
+    const int pair = min(rg * 64 + lane, (A.nv - 1) / 2);
+    double Dz[2], iz[2], L[2];
+    bool parz[2];
+    double win0 = 1e300, win1 = -1e300;
+    {
+        const double zlo = A.own_lo - 0.5, zhi = A.own_hi - 0.5;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            Dz[r] = ((2 * pair + r - A.cv) * A.dv + A.offv) / A.dz;
+            const double mz = Dz[r] * A.dz;
+            L[r] = sqrt(Lxy2 + mz * mz);
+            parz[r] = fabs(mz) < 1e-12 * L[r];
+            if (fabs(mz) < 1e-12 * Lref) {
+                iz[r] = 0.0;
+                if (G.S[2] >= zlo && G.S[2] <= zhi) {
+                    win0 = fmin(win0, t0);
+                    win1 = fmax(win1, t1);
+                }
+            } else {
+                iz[r] = 1.0 / Dz[r];
+                const double ta = (zlo - G.S[2]) * iz[r], tb = (zhi - G.S[2]) * iz[r];
+                win0 = fmin(win0, fmin(ta, tb));
+                win1 = fmax(win1, fmax(ta, tb));
+            }
+        }
+    }
+    // the wave walks only where one of its rows is inside the owned slices
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        win0 = fmin(win0, __shfl_xor(win0, off, 64));
+        win1 = fmax(win1, __shfl_xor(win1, off, 64));
+    }
+    t0 = fmax(t0, win0 - 1e-9);
+    t1 = fmin(t1, win1 + 1e-9);
+    hit = hit && t0 < t1;
+
+    float acc0 = 0.0f, acc1 = 0.0f;
+    if (hit) {
+        ZPairRows Z;
+        // slot coordinate: voxel mem_lo + k spans [k + 1, k + 2)
+        const double ze = G.S[2] - A.mem_lo + t0 * Dz[0] + 1.5, ze2 = G.S[2] - A.mem_lo + t0 * Dz[1] + 1.5;
+        const double k0 = floor(ze);
+        // a row parallel to the slices crosses no plane: an inverse slope beyond any time, either way
+        const double far = 1e30;
+        Z.Zr = (float)(ze - k0);
+        Z.Dz = parz[0] ? 0.0f : (float)Dz[0];
+        Z.inv = (float)(parz[0] ? far : iz[0]);
+        Z.c1 = (float)((1.0 - (ze - k0)) * (parz[0] ? far : iz[0]));
+        Z.inv2 = (float)(parz[1] ? far : iz[1]);
+        Z.c2 = (float)((1.0 - (ze2 - k0)) * (parz[1] ? far : iz[1]));
+        Z.up = parz[0] || Dz[0] > 0.0;
+        Z.up2 = parz[1] || Dz[1] > 0.0;
+        // |k0| < 2^22 (checked on the host), so these are exact in FP32
+        Z.lmin = (float)(-1.0 - k0);
+        Z.lmax = (float)((double)nzc - k0);
+        Z.kb = (uint32_t)(((int64_t)k0 + 1) * (int64_t)sizeof(TV));
+        // both rows inside the held slices from t0 to t1 (a row's z is monotonic)
+        const double z1 = ze + (t1 - t0) * Dz[0], z2 = ze2 + (t1 - t0) * Dz[1], top = (double)nzc + 1.0;
+        const bool inside = ze >= 1.0 && z1 >= 1.0 && ze <= top && z1 <= top && ze2 <= top && z2 <= top;
+        ZPath P;
+        P.nx = A.nx;
+        P.maxp = A.nx + A.ny + 66;
+        P.Te = (float)(t1 - t0);
+        // delta = t dv / dz reaches 1
+        P.ts = (float)(A.dz / A.dv - t0);
+        const int ihi[2] = {A.nx - 1, A.ny - 1};
+#pragma unroll
+        for (int ax = 0; ax < 2; ++ax) {
+            const double E = G.S[ax] + t0 * D[ax];
+            int i = (int)floor(E + 0.5);
+            i = i < 0 ? 0 : (i > ihi[ax] ? ihi[ax] : i);
+            P.idx[ax] = i;
+            if (par[ax]) {
+                P.sg[ax] = 0;
+                P.t0[ax] = FLT_MAX;
+                P.dt[ax] = 0.0f;
+            } else {
+                const int s = D[ax] > 0 ? 1 : -1;
+                P.sg[ax] = s;
+                P.t0[ax] = (float)((0.5 - s * (E - i)) * inv[ax]);
+                P.dt[ax] = (float)inv[ax];
+                const int nexit = s > 0 ? ihi[ax] - i : i;
+                P.Te = fminf(P.Te, fmaf((float)nexit, P.dt[ax], P.t0[ax]));
+            }
+        }
+        // uniform over the wave
+        auto uni = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
+#pragma unroll
+        for (int ax = 0; ax < 2; ++ax) {
+            P.t0[ax] = uni(P.t0[ax]);
+            P.dt[ax] = uni(P.dt[ax]);
+            P.idx[ax] = __builtin_amdgcn_readfirstlane(P.idx[ax]);
+            P.sg[ax] = __builtin_amdgcn_readfirstlane(P.sg[ax]);
+        }
+        P.Te = uni(P.Te);
+        P.ts = uni(P.ts);
+        const bool up = __all(Z.up && Z.up2), down = __all(!Z.up && !Z.up2), in = __all(inside);
+        if (up) {
+            if (in) zp_walk<1, false>(vz, nzp, P, Z, acc0, acc1);
+            else zp_walk<1, true>(vz, nzp, P, Z, acc0, acc1);
+        } else if (down) {
+            if (in) zp_walk<-1, false>(vz, nzp, P, Z, acc0, acc1);
+            else zp_walk<-1, true>(vz, nzp, P, Z, acc0, acc1);
+        } else {
+            zp_walk<0, true>(vz, nzp, P, Z, acc0, acc1);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int b = 2 * (rg * 64 + lane) + r;
+        if (b >= A.nv) continue;
+        const int64_t o = ((int64_t)ai * A.nv + b) * A.nu + a;
+        const float prev = A.accumulate ? to_f(proj[o]) : 0.0f;
+        proj[o] = from_f<TP>(prev + (float)((r ? acc1 : acc0) * L[r]));
+    }
+}
+
 // [z][y][x] -> column-major slots: slices [0, nz) of src go to slots slot0 + z of columns of nzp
-// slots ([y][x][slot]); pads: bit 0 zeroes slot 0, bit 1 zeroes slot nzp - 1.  32 x 32 (z, x) tiles.
+// slots ([y][x][slot]); pads: bit 0 zeroes slot 0 (and the guard element before the first column), bit 1
+// zeroes slot nzp - 1 (and the guard elements after the last).  32 x 32 (z, x) tiles.
 // Values pass through FP32 (exact for the storage types), so the copy may also change the type.
 template <typename TS, typename TD>
 __global__ __launch_bounds__(256) void k_zcols(const TS *__restrict__ src, TD *__restrict__ dst, int nx, int ny, int nz,
@@ -667,8 +996,15 @@ __global__ __launch_bounds__(256) void k_zcols(const TS *__restrict__ src, TD *_
         const int x = x0 + threadIdx.x;
         if (x < nx) {
             const int64_t c = ((int64_t)y * nx + x) * nzp;
-            if ((pads & 1) && blockIdx.y == 0) dst[c] = from_f<TD>(0.0f);
-            if ((pads & 2) && blockIdx.y == gridDim.y - 1) dst[c + nzp - 1] = from_f<TD>(0.0f);
+            if ((pads & 1) && blockIdx.y == 0) {
+                dst[c] = from_f<TD>(0.0f);
+                if (x == 0 && y == 0) dst[-1] = from_f<TD>(0.0f);
+            }
+            if ((pads & 2) && blockIdx.y == gridDim.y - 1) {
+                dst[c + nzp - 1] = from_f<TD>(0.0f);
+                if (x == nx - 1 && y == ny - 1)
+                    for (int e = 0; e < ZCOL_GUARD; ++e) dst[c + nzp + e] = from_f<TD>(0.0f);
+            }
         }
     }
 }
@@ -1226,6 +1562,23 @@ bool zcol_ok(const ct_plan *p, int64_t a0, int64_t a1) {
     return true;
 }
 
+// Neighbouring rows of a detector column stay less than two slots apart: t dv / dz < 2 at the largest ray
+// parameter t of the grid, its largest depth over the source-detector distance.
+static bool zpair_ok(const ct_plan *p, int64_t a0, int64_t a1) {
+    const ct_geometry &g = p->g;
+    double tmax = 0.0;
+    for (int64_t i = a0; i < a1; ++i) {
+        const AngleGeo &G = p->tab[(size_t)i];
+        double depth = 0.0;  // M's third row: the depth of voxel (i, j, k), over the grid box's corners
+        for (int c = 0; c < 4; ++c) {
+            const double x = (c & 1) ? g.nVoxel[0] - 0.5 : -0.5, y = (c & 2) ? g.nVoxel[1] - 0.5 : -0.5;
+            depth = std::max(depth, G.M[8] * x + G.M[9] * y + G.M[11]);
+        }
+        tmax = std::max(tmax, depth / G.DSDv);
+    }
+    return std::min(tmax, 1.0) * g.dDetector[1] / g.dVoxel[2] < 1.999;
+}
+
 ct_status launch_forward(ct_plan *p, ct_projector kind, const void *vol, ct_dtype vt, void *proj, ct_dtype pt,
                          int accumulate, int64_t a0, int64_t a1, const Slab &slab, hipStream_t st,
                          const void *vcopy) {
@@ -1246,28 +1599,23 @@ ct_status launch_forward(ct_plan *p, ct_projector kind, const void *vol, ct_dtyp
         void *vz = const_cast<void *>(vcopy);
         void *own_z = nullptr;
         if (!vz) {
-            const size_t zbytes = (size_t)(nx * ny * (nz + 2)) * dtype_size(vt);
-            if (CT_MALLOC_ASYNC(&own_z, zbytes, st) == hipSuccess) {
-                ct_status zs = launch_zcols(vol, vt, own_z, nx, ny, nz, st);
+            if (CT_MALLOC_ASYNC(&own_z, zcol_bytes(g, dtype_size(vt)), st) == hipSuccess) {
+                vz = zcol_base(own_z, dtype_size(vt));
+                ct_status zs = launch_zcols(vol, vt, vz, nx, ny, nz, st);
                 if (zs != CT_OK) return zs;
-                vz = own_z;
             } else {
                 (void)hipGetLastError();
             }
         }
         if (vz) {
             const int64_t nu = g.nDetector[0], nv = g.nDetector[1];
+            // neighbouring rows in pairs where the upper row of a pair stays less than two slots above the
+            // lower one; else rows 64 apart, two per lane when the launch fills the chip with them
+            // (a wave takes 128 rows in pairs: up to 64 rows would leave half of its lanes idle, 64^3 / 64
+            // angles of 64^2 31 -> 40 us)
             const int64_t cblocks = (nu + ZC_COLS - 1) / ZC_COLS;
-            // two rows per lane when the launch is large enough to fill the chip with them
-#ifdef CT_ZC_ROWS
-            const int rows = CT_ZC_ROWS;
-#else
-#ifndef CT_IC_ROWS
-            const int rows = cblocks * (a1 - a0) * ((nv + 127) / 128) >= 4096 ? 2 : 1;
-#else
-            const int rows = CT_IC_ROWS;
-#endif
-#endif
+            const bool pair = nv > 64 && zpair_ok(p, a0, a1);
+            const int rows = pair || cblocks * (a1 - a0) * ((nv + 127) / 128) >= 4096 ? 2 : 1;
             const int64_t rgroups = (nv + 64 * rows - 1) / (64 * rows);
             const int64_t max_ang = angles_per_launch(cblocks * rgroups, 64 * ZC_COLS);
             const size_t proj_angle = (size_t)nu * nv * dtype_size(pt);
@@ -1278,14 +1626,11 @@ ct_status launch_forward(ct_plan *p, ct_projector kind, const void *vol, ct_dtyp
                 A.rgroups = (int32_t)rgroups;
                 char *pp = (char *)proj + (size_t)(c0 - a0) * proj_angle;
                 const dim3 grid((unsigned)(cblocks * (c1 - c0) * rgroups)), block(64 * ZC_COLS);
-#ifdef CT_ZC_ROWS
-                if (rows == 4) {
+                if (pair) {
                     CT_DISPATCH2(vt, TV, pt, TP,
-                                 hipLaunchKernelGGL((k_siddon_col<TV, TP, 4>), grid, block, 0, st, (const TV *)vz,
+                                 hipLaunchKernelGGL((k_siddon_pair<TV, TP>), grid, block, 0, st, (const TV *)vz,
                                                     (TP *)pp, A));
-                } else
-#endif
-                if (rows == 2) {
+                } else if (rows == 2) {
                     CT_DISPATCH2(vt, TV, pt, TP,
                                  hipLaunchKernelGGL((k_siddon_col<TV, TP, 2>), grid, block, 0, st, (const TV *)vz,
                                                     (TP *)pp, A));

@@ -278,7 +278,9 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
     CT_HIP(hipStreamCreateWithFlags(&S.h2d, hipStreamNonBlocking));
     CT_HIP(hipStreamCreateWithFlags(&S.d2h, hipStreamNonBlocking));
     DevBuf slab, stage, dbuf[3];
-    CT_HIP(CT_MALLOC(&slab.p, (L.h + (L.col ? 2 : 2 * L.halo)) * slice));
+    // (a column-major slab lies between its guard elements)
+    CT_HIP(CT_MALLOC(&slab.p, (L.h + (L.col ? 2 : 2 * L.halo)) * slice + 2 * ZCOL_GUARD * dtype_size(vt)));
+    void *const cols = zcol_base(slab.p, dtype_size(vt));
     if (L.col) CT_HIP(CT_MALLOC(&stage.p, ZSTAGE * slice));
     for (auto &b : dbuf) CT_HIP(CT_MALLOC(&b.p, chunk_bytes));
     HostBuf sin[3], sout[3], svol[2];
@@ -363,7 +365,7 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
                 const int64_t zn = std::min(ZSTAGE, own_hi - z0);
                 if ((s = upload(stage.p, (const char *)h_vol + z0 * slice, zn * slice)) != CT_OK) return s;
                 const int pads = (z0 == own_lo ? 1 : 0) | (z0 + zn == own_hi ? 2 : 0);
-                if ((s = launch_zcols_piece(stage.p, vt, slab.p, g.nVoxel[0], g.nVoxel[1], zn, nzp, 1 + (z0 - own_lo),
+                if ((s = launch_zcols_piece(stage.p, vt, cols, g.nVoxel[0], g.nVoxel[1], zn, nzp, 1 + (z0 - own_lo),
                                             pads, S.comp)) != CT_OK)
                     return s;
                 CT_HIP(hipStreamSynchronize(S.comp));  // the stage is reused by the next piece
@@ -429,7 +431,7 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
             }
             CT_HIP(hipEventRecord(tk0.e[c], S.comp));
             if ((s = launch_forward(p, kind, slab.p, vt, dbuf[j].p, pt, acc ? 1 : 0, a0, a1, sl, S.comp,
-                                    L.col ? slab.p : nullptr)) != CT_OK)
+                                    L.col ? cols : nullptr)) != CT_OK)
                 return s;
             CT_HIP(hipEventRecord(tk1.e[c], S.comp));
             CT_HIP(hipEventRecord(ev_k.e[j], S.comp));
