@@ -1161,40 +1161,49 @@ __global__ __launch_bounds__(256) void k_sart_update(const float *__restrict__ r
 
 // The same update on the column-major copy ([y][x][slot], slot k + 1 = voxel k) with the residual
 // transposed to [u][v].
-#ifndef CT_SART_R
-#define CT_SART_R 8
-#endif
-constexpr int SART_R = CT_SART_R;  // voxels per lane of the column update
-
-// One wave per voxel column and group of 64 SART_R heights (lane = height, SART_R heights 64 apart):
-// the column's detector coordinate, FDK weight and column taps are set up once, and the lanes read
-// the transposed residual rT[u][v] at consecutive rows and update consecutive slots of the
-// column-major copy.
+// One wave per voxel column and group of 64 R heights (lane = height, R heights 64 apart); it updates
+// consecutive slots of the column-major copy.  The column's detector coordinate, FDK weight and two
+// residual columns are the same for the whole wave.
+//
+// R <= 4: the lanes first form the residual at that coordinate, times the weight, for every detector row that
+// the heights meet (lane = row: coalesced reads of the transposed residual rT[u][v]) into LDS (hrows rows per
+// wave), and each height interpolates between two neighbouring rows there: the four taps per height cost
+// the address unit up to 53 cycles per 64 voxel angles (a dword load whose lanes skip rows takes 13), the
+// two coalesced reads about 11.  R > 4: the taps are read per height, all in flight together; the rows of
+// so many heights take several rounds of loads, whose latency the fewer waves do not hide.  OS-SART sweeps
+// with R = 4 in the new form / in the old one / with R = 8 (whose upper half was idle): 256^3, 180 angles by
+// 18 4.6 / - / 6.8 ms; subsets of 10 angles, per tap / through LDS: 512^3 (R = 8) 9.4 / 10.2 ms, 384^3 (R = 6
+// / 4) 3.9 / 4.5 ms, 301 x 290 x 300 3.3 / 3.7 ms.
+constexpr int SART_G = 16;  // angles whose references are formed together
+constexpr int SART_LD = 2;  // loads of 64 rows (from each residual column) in flight (1 / 2 / 4: 5.0 / 4.6 / 4.9 ms)
+template <int R>
 __global__ __launch_bounds__(256) void k_sart_update_col(const float *__restrict__ rT, float *__restrict__ vz,
-                                                         BpArgs A, float lambda, int zwaves) {
+                                                         BpArgs A, float lambda, int zwaves, int hrows) {
     // per wave and angle: the column's detector coordinate a* (origin and fraction), FDK weight and
     // row step per mm; per height group r, the row coordinate of the group's reference height
     // (origin and fraction).  All from FP64, so the FP32 per-height parts are a few pixels in size.
     struct ColRef {
         float fa, w, mv, ia;
     };
-    __shared__ ColRef hdr[4][64];
-    __shared__ float2 bref[4][64][SART_R];
+    __shared__ ColRef hdr[4][SART_G];
+    __shared__ float2 bref[4][SART_G][R];
+    extern __shared__ float hbuf[];  // hrows per wave
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
     const int64_t gw = (int64_t)blockIdx.x * 4 + wave;
     const int64_t ncol = (int64_t)A.nx * A.ny;
     const bool live = gw / zwaves < ncol;
     const int64_t col = live ? gw / zwaves : ncol - 1;  // a wave past the last column writes nothing
-    const int zbase = (int)(gw % zwaves) * 64 * SART_R;
+    const int zbase = (int)(gw % zwaves) * 64 * R;
     const int kk0 = zbase + lane;
     const int i = (int)(col % A.nx), j = (int)(col / A.nx);
     const int64_t pix = (int64_t)A.nu * A.nv;
     float *vc = vz + col * (A.nz + 2) + 1;
+    float *hw = hbuf + wave * hrows;
     // the voxels' values are read first, so their loads overlap the first angle's taps
-    float xo[SART_R], kref[SART_R], zl[SART_R];
+    float xo[R], kref[R], zl[R];
 #pragma unroll
-    for (int r = 0; r < SART_R; ++r) {
+    for (int r = 0; r < R; ++r) {
         const int kk = min(kk0 + 64 * r, A.nz - 1);
         xo[r] = vc[kk];
         kref[r] = tile_mid(min(zbase + 64 * r, A.nz - 1), 64, A.nz);
@@ -1203,15 +1212,15 @@ __global__ __launch_bounds__(256) void k_sart_update_col(const float *__restrict
     const double xc = A.dx0 + i * A.ddx, yc = A.dy0 + j * A.ddy;
     const float amax = (float)A.nu + 1.0f, bmax = (float)A.nv + 1.0f;
     // sums over the subset's angles, in angle order
-    float num[SART_R], V[SART_R];
+    float num[R], V[R];
 #pragma unroll
-    for (int r = 0; r < SART_R; ++r) num[r] = V[r] = 0.0f;
-    for (int t0 = 0; t0 < A.nang; t0 += 64) {
-        const int nk = min(64, A.nang - t0);
+    for (int r = 0; r < R; ++r) num[r] = V[r] = 0.0f;
+    for (int t0 = 0; t0 < A.nang; t0 += SART_G) {
+        const int nk = min(SART_G, A.nang - t0);
         __syncthreads();
         // lane = (angle, height group) pair, so a launch of one angle (SART) costs one pass
-        for (int p0 = 0; p0 < nk * SART_R; p0 += 64) {
-            const int q = (p0 + lane) / SART_R, r = (p0 + lane) % SART_R;
+        for (int p0 = 0; p0 < nk * R; p0 += 64) {
+            const int q = (p0 + lane) / R, r = (p0 + lane) % R;
             if (q < nk) {
                 const AngleGeo &G = A.tab[A.a0 + t0 + q];
                 const double D = A.dDSO - (xc * G.c + yc * G.s), iD = rcp_f64(D);
@@ -1240,37 +1249,86 @@ __global__ __launch_bounds__(256) void k_sart_update_col(const float *__restrict
             const float *rt = rT + (t0 + q) * pix;
             const float *r0 = rt + (int64_t)clampi(ia, 0, A.nu - 1) * A.nv;
             const float *r1 = rt + (int64_t)clampi(ia + 1, 0, A.nu - 1) * A.nv;
-            const float w = H.w;
-            const float wva = w * (wa0 + wa1);
-            // all taps of the wave's SART_R heights first (heights clamped into the column), then the sums
-            float wb0[SART_R], wb1[SART_R], t00[SART_R], t01[SART_R], t10[SART_R], t11[SART_R];
+            if constexpr (R > 4) {
+                const float w = H.w;
+                const float wva = w * (wa0 + wa1);
+                // all taps of the wave's R heights first (heights clamped into the column), then the sums
+                float wb0[R], wb1[R], t00[R], t01[R], t10[R], t11[R];
 #pragma unroll
-            for (int r = 0; r < SART_R; ++r) {
+                for (int r = 0; r < R; ++r) {
+                    const float2 B = bref[wave][q][r];
+                    const float bs = fmaf(zl[r], H.mv, B.y);
+                    const float bf = floorf(bs);
+                    const float fb = bs - bf;
+                    const int ib = (int)__builtin_amdgcn_fmed3f(B.x + bf, -2.0f, bmax);
+                    wb0[r] = ((unsigned)ib < (unsigned)A.nv) ? 1.0f - fb : 0.0f;
+                    wb1[r] = ((unsigned)(ib + 1) < (unsigned)A.nv) ? fb : 0.0f;
+                    const int b0 = clampi(ib, 0, A.nv - 1), b1 = clampi(ib + 1, 0, A.nv - 1);
+                    t00[r] = r0[b0];
+                    t10[r] = r1[b0];
+                    t01[r] = r0[b1];
+                    t11[r] = r1[b1];
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float v0 = fmaf(wa1, t10[r], wa0 * t00[r]);
+                    const float v1 = fmaf(wa1, t11[r], wa0 * t01[r]);
+                    num[r] += w * fmaf(wb1[r], v1, wb0[r] * v0);
+                    V[r] += wva * (wb0[r] + wb1[r]);
+                }
+                continue;
+            }
+            const float w0 = H.w * wa0, w1 = H.w * wa1;
+            // the heights' lower tap rows (rising with the height) and fractions
+            int ib[R];
+            float fb[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
                 const float2 B = bref[wave][q][r];
                 const float bs = fmaf(zl[r], H.mv, B.y);
                 const float bf = floorf(bs);
-                const float fb = bs - bf;
-                const int ib = (int)__builtin_amdgcn_fmed3f(B.x + bf, -2.0f, bmax);
-                wb0[r] = ((unsigned)ib < (unsigned)A.nv) ? 1.0f - fb : 0.0f;
-                wb1[r] = ((unsigned)(ib + 1) < (unsigned)A.nv) ? fb : 0.0f;
-                const int b0 = clampi(ib, 0, A.nv - 1), b1 = clampi(ib + 1, 0, A.nv - 1);
-                t00[r] = r0[b0];
-                t10[r] = r1[b0];
-                t01[r] = r0[b1];
-                t11[r] = r1[b1];
+                fb[r] = bs - bf;
+                ib[r] = (int)__builtin_amdgcn_fmed3f(B.x + bf, -2.0f, bmax);
             }
+            const int lo = __builtin_amdgcn_readfirstlane(ib[0]);
+            // (one row more than the top height's: a group's reference rounds its rows apart from another's)
+            const int nrow = min(__builtin_amdgcn_readlane(ib[R - 1], 63) + 3 - lo, hrows);
+            for (int n0 = 0; n0 < nrow; n0 += 64 * SART_LD) {
+                float p0[SART_LD], p1[SART_LD];
 #pragma unroll
-            for (int r = 0; r < SART_R; ++r) {
-                const float v0 = fmaf(wa1, t10[r], wa0 * t00[r]);
-                const float v1 = fmaf(wa1, t11[r], wa0 * t01[r]);
-                num[r] += w * fmaf(wb1[r], v1, wb0[r] * v0);
-                V[r] += wva * (wb0[r] + wb1[r]);
+                for (int m = 0; m < SART_LD; ++m) {
+                    const int b = clampi(lo + n0 + 64 * m + lane, 0, A.nv - 1);
+                    p0[m] = r0[b];
+                    p1[m] = r1[b];
+                }
+#pragma unroll
+                for (int m = 0; m < SART_LD; ++m) {
+                    const int n = n0 + 64 * m + lane;
+                    const float h = fmaf(w1, p1[m], w0 * p0[m]);
+                    if (n < nrow) hw[n] = (unsigned)(lo + n) < (unsigned)A.nv ? h : 0.0f;  // zero off the detector
+                }
             }
+            wave_lds_sync();
+            const bool in = lo >= 0 && lo + nrow <= A.nv;  // every tap is on the detector
+            const float wv = w0 + w1;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float *h = hw + clampi(ib[r] - lo, 0, nrow - 2);
+                num[r] += fmaf(fb[r], h[1] - h[0], h[0]);
+                if (in) {
+                    V[r] += wv;
+                } else {
+                    const float b0 = (unsigned)ib[r] < (unsigned)A.nv ? 1.0f - fb[r] : 0.0f;
+                    const float b1 = (unsigned)(ib[r] + 1) < (unsigned)A.nv ? fb[r] : 0.0f;
+                    V[r] += wv * (b0 + b1);
+                }
+            }
+            wave_lds_sync();
         }
     }
     if (!live) return;
 #pragma unroll
-    for (int r = 0; r < SART_R; ++r) {
+    for (int r = 0; r < R; ++r) {
         const int kk = kk0 + 64 * r;
         // num / V through the hardware reciprocal (within 1 ulp)
         if (kk < A.nz && V[r] > 1e-6f) vc[kk] = fmaf(lambda, num[r] * __builtin_amdgcn_rcpf(V[r]), xo[r]);
@@ -1426,6 +1484,35 @@ BpArgs make_bp_args(ct_plan *p, const AngleGeo *tab, int64_t a0, int64_t a1, con
     return A;
 }
 
+// Detector rows that 64 R heights of a voxel column can meet, at most, with the second tap and a margin: a
+// height step is dz m / dv rows, the magnification m at most DSD / (DSO - R').
+constexpr int64_t SART_MAX_ROWS = 2048;  // 32 KiB of LDS per block
+int64_t sart_rows(const ct_geometry &g, int R) {
+    double rad = 0.0;
+    for (int c = 0; c < 4; ++c)
+        rad = std::max(rad, std::hypot(g.offOrigin[0] + ((c & 1) ? 0.5 : -0.5) * g.nVoxel[0] * g.dVoxel[0],
+                                       g.offOrigin[1] + ((c & 2) ? 0.5 : -0.5) * g.nVoxel[1] * g.dVoxel[1]));
+    const double rows = (std::min<int64_t>(64 * R, g.nVoxel[2]) - 1) * g.dVoxel[2] * g.DSD / (g.DSO - rad) / g.dDetector[1];
+    return rows < 1e9 ? (int64_t)rows + 6 : int64_t(1) << 30;
+}
+
+// Voxels per lane R of the kernels whose waves take 64 R voxels of a column: a wave sets up each (angle,
+// detector column) once for them, which costs about 2/R of the per-voxel work; the R that minimises
+// (voxels covered, idle lanes included) x (1 + 2/R).
+int lane_voxels(int64_t nz) {
+    int R = 8;
+    double best = DBL_MAX;
+    for (int r : {8, 6, 4, 2, 1}) {
+        const int64_t covered = (nz + 64 * r - 1) / (64 * r) * (64 * r);
+        const double cost = (double)covered * (1.0 + 2.0 / r);
+        if (cost < best) {  // ties keep the larger R
+            best = cost;
+            R = r;
+        }
+    }
+    return R;
+}
+
 }  // namespace
 
 // CT_VIEWS_ADJ_DIRECT=1 or 2 sends the exact adjoint of vertical views to a per-view kernel (tests
@@ -1528,19 +1615,7 @@ ct_status launch_backproject(ct_plan *p, ct_backprojector kind, const void *proj
         }
         if (nr <= 4 && yq && qcap >= per_angle) {
             const int64_t kq = std::min<int64_t>(a1 - a0, (int64_t)(qcap / per_angle));
-            // voxels per lane R: a wave covers 64 R voxels of its column and sets up each (angle,
-            // detector column) once for them, which costs about 2/R of the per-voxel work; pick the
-            // R that minimises (voxels covered, idle lanes included) x (1 + 2/R)
-            int R = 8;
-            double best = DBL_MAX;
-            for (int r : {8, 6, 4, 2, 1}) {
-                const int64_t covered = (nzown + 64 * r - 1) / (64 * r) * (64 * r);
-                const double cost = (double)covered * (1.0 + 2.0 / r);
-                if (cost < best) {  // ties keep the larger R
-                    best = cost;
-                    R = r;
-                }
-            }
+            int R = lane_voxels(nzown);
 #ifdef CT_ADJ_R
             R = CT_ADJ_R;
 #endif
@@ -1671,6 +1746,11 @@ ct_status backproject_noalloc(ct_plan *p, ct_backprojector kind, const void *pro
     return launch_backproject(p, kind, proj, pt, vol, vt, accumulate, a0, a1, sl, st, scr, NOALLOC_SCRATCH_BYTES);
 }
 
+bool sart_col_ok(const ct_plan *p) {
+    return !p->views && (lane_voxels(p->g.nVoxel[2]) > 4 ||
+                         std::min<int64_t>(sart_rows(p->g, 1), p->g.nDetector[1] + 4) <= SART_MAX_ROWS);
+}
+
 ct_status launch_sart_update(ct_plan *p, const float *r, float *vol, int64_t a0, int64_t a1, float lambda,
                              hipStream_t st) {
     const AngleGeo *tab = nullptr;
@@ -1690,10 +1770,22 @@ ct_status launch_sart_update_col(ct_plan *p, const float *rT, float *vz, int64_t
     ct_status s = plan_device_table(p, st, &tab);
     if (s != CT_OK) return s;
     BpArgs A = make_bp_args(p, tab, a0, a1, full_slab(p->g), 1);
-    const int zwaves = (A.nz + 64 * SART_R - 1) / (64 * SART_R);
+    int R = lane_voxels(A.nz);
+    while (R > 1 && R <= 4 && sart_rows(p->g, R) > SART_MAX_ROWS) R /= 2;
+    const int hrows = R > 4 ? 0 : (int)std::min<int64_t>(sart_rows(p->g, R), A.nv + 4);
+    const int zwaves = (A.nz + 64 * R - 1) / (64 * R);
     const int64_t waves = (int64_t)A.nx * A.ny * zwaves;
-    hipLaunchKernelGGL(k_sart_update_col, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, rT, vz, A, lambda,
-                       zwaves);
+#define CT_SART_U(RR)                                                                                                  \
+    hipLaunchKernelGGL((k_sart_update_col<RR>), dim3((unsigned)((waves + 3) / 4)), dim3(256),                          \
+                       (size_t)4 * hrows * sizeof(float), st, rT, vz, A, lambda, zwaves, hrows)
+    switch (R) {
+        case 1: CT_SART_U(1); break;
+        case 2: CT_SART_U(2); break;
+        case 4: CT_SART_U(4); break;
+        case 6: CT_SART_U(6); break;
+        default: CT_SART_U(8); break;
+    }
+#undef CT_SART_U
     CT_HIP(hipGetLastError());
     return CT_OK;
 }
