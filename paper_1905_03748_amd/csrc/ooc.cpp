@@ -31,6 +31,9 @@ namespace {
 constexpr uint64_t RESERVE = 64ull << 20;      // angle table, allocator slack
 constexpr int64_t ZSTAGE = 8;                   // slices per column-major upload piece
 constexpr size_t STAGE_PIECE = 64ull << 20;    // slab staging piece
+// pageable slabs are sent in pieces of this size where they can: each first write to a page of a new
+// pinned buffer faults it in (512^3: pieces of 16 / 32 / 64 MiB 29.4 / 30.8 / 33 ms)
+constexpr size_t UPLOAD_PIECE = 16ull << 20;
 
 using clk = std::chrono::steady_clock;
 double secs(clk::time_point a, clk::time_point b) { return std::chrono::duration<double>(b - a).count(); }
@@ -44,21 +47,35 @@ bool verbose() {
     return v;
 }
 
+// f(0) .. f(n - 1) on n host threads; what a thread cannot be started for runs on this one
+template <typename F>
+void par_for(int n, F f) {
+    std::vector<std::thread> th;
+    int i = 0;
+    try {
+        th.reserve((size_t)n);
+        for (; i + 1 < n; ++i) th.emplace_back(f, i);
+    } catch (...) {
+    }
+    for (; i < n; ++i) f(i);
+    for (auto &t : th) t.join();
+}
+constexpr int COPY_THREADS = 8;
+// Copies from this size on are worth the threads: one thread moves 4 MiB into a new pinned buffer in about a
+// millisecond, eight are started in a tenth of it (512^3, 60 angles, whose chunks of rows are 9 MiB: from 16
+// / 8 / 4 MiB on 45.6 / 29.9 / 29.4 ms).
+constexpr size_t PAR_BYTES = 4u << 20;
+
 void par_memcpy(void *dst, const void *src, size_t n) {
-    if (n < (16u << 20)) {
+    if (n < PAR_BYTES) {
         std::memcpy(dst, src, n);
         return;
     }
-    const int nt = 8;
-    std::vector<std::thread> th;
-    const size_t part = (n + nt - 1) / nt;
-    for (int i = 0; i < nt; ++i) {
-        const size_t o = i * part;
-        if (o >= n) break;
-        const size_t len = std::min(part, n - o);
-        th.emplace_back([=] { std::memcpy((char *)dst + o, (const char *)src + o, len); });
-    }
-    for (auto &t : th) t.join();
+    const size_t part = (n + COPY_THREADS - 1) / COPY_THREADS;
+    par_for(COPY_THREADS, [=](int i) {
+        const size_t o = std::min(n, (size_t)i * part), len = std::min(part, n - o);
+        std::memcpy((char *)dst + o, (const char *)src + o, len);
+    });
 }
 
 bool is_pinned(const void *p) {
@@ -233,8 +250,18 @@ ct_status copy_rows(void *dst, const void *src, size_t pangle, size_t rowb, int6
 // the same between host buffers (staging), in parallel for large bands
 void host_rows(void *dst, const void *src, size_t pangle, size_t rowb, int64_t b0, int64_t b1, int64_t n) {
     if (b1 <= b0) return;
-    for (int64_t a = 0; a < n; ++a)
-        par_memcpy((char *)dst + a * pangle + b0 * rowb, (const char *)src + a * pangle + b0 * rowb, (b1 - b0) * rowb);
+    const size_t band = (size_t)(b1 - b0) * rowb;
+    if (band >= PAR_BYTES) {
+        for (int64_t a = 0; a < n; ++a)
+            par_memcpy((char *)dst + a * pangle + b0 * rowb, (const char *)src + a * pangle + b0 * rowb, band);
+        return;
+    }
+    // smaller bands: the angles are shared out over the threads
+    const int nt = band * (size_t)n < PAR_BYTES ? 1 : (int)std::min<int64_t>(COPY_THREADS, n);
+    par_for(nt, [=](int i) {
+        for (int64_t a = n * i / nt; a < n * (i + 1) / nt; ++a)
+            std::memcpy((char *)dst + a * pangle + b0 * rowb, (const char *)src + a * pangle + b0 * rowb, band);
+    });
 }
 
 }  // namespace
@@ -293,9 +320,9 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
     if (!vol_pinned)
         for (auto &b : svol) CT_HIP(CT_HOST_MALLOC(&b.p, STAGE_PIECE));
     st.t_pin_s += secs(tp, clk::now());
-    Events ev_h2d, ev_k, ev_d2h, ev_vol, tk0, tk1;
+    Events ev_h2d, ev_k, ev_d2h, ev_vol, ev_up, tk0, tk1;
     if ((s = ev_h2d.make(3)) != CT_OK || (s = ev_k.make(3)) != CT_OK || (s = ev_d2h.make(3)) != CT_OK ||
-        (s = ev_vol.make(2)) != CT_OK)
+        (s = ev_vol.make(2)) != CT_OK || (s = ev_up.make(2)) != CT_OK)
         return s;
     tk0.e.resize(nchunks, nullptr);
     tk1.e.resize(nchunks, nullptr);
@@ -359,17 +386,57 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
             return CT_OK;
         };
         if (L.col) {
-            // column-major slab: pieces of ZSTAGE slices through the stage, transposed into place
+            // Column-major slab: pieces of ZSTAGE slices through the device stage, transposed into place.
+            // The stage passes between the copy stream and the compute stream by events, and a pageable
+            // volume is copied into one pinned buffer, as many slices at a time as it holds, while the
+            // other is sent, so the host waits for a buffer only (512^3 in two slabs, 60 angles: 62 ->
+            // 29 ms with the rows' copies on threads too; the host copied 8 slices on one thread, waited for them and for their transpose).
             const int64_t nzp = (own_hi - own_lo) + 2;
-            for (int64_t z0 = own_lo; z0 < own_hi; z0 += ZSTAGE) {
-                const int64_t zn = std::min(ZSTAGE, own_hi - z0);
-                if ((s = upload(stage.p, (const char *)h_vol + z0 * slice, zn * slice)) != CT_OK) return s;
+            const size_t piece = std::max<size_t>(UPLOAD_PIECE, (size_t)ZSTAGE * slice);
+            const int64_t fit = piece <= STAGE_PIECE ? (int64_t)(piece / slice) / ZSTAGE * ZSTAGE : 0;
+            const bool whole = vol_pinned || fit > 0;  // a pinned buffer holds a piece
+            const int64_t nhost = vol_pinned ? own_hi - own_lo : std::max(fit, ZSTAGE);
+            bool used[2] = {false, false}, staged = false;
+            int q = 0;
+            auto transpose = [&](int64_t z0, int64_t zn) -> ct_status {
+                CT_HIP(hipEventRecord(ev_up.e[0], S.h2d));
+                CT_HIP(hipStreamWaitEvent(S.comp, ev_up.e[0], 0));
                 const int pads = (z0 == own_lo ? 1 : 0) | (z0 + zn == own_hi ? 2 : 0);
-                if ((s = launch_zcols_piece(stage.p, vt, cols, g.nVoxel[0], g.nVoxel[1], zn, nzp, 1 + (z0 - own_lo),
-                                            pads, S.comp)) != CT_OK)
-                    return s;
-                CT_HIP(hipStreamSynchronize(S.comp));  // the stage is reused by the next piece
+                ct_status e = launch_zcols_piece(stage.p, vt, cols, g.nVoxel[0], g.nVoxel[1], zn, nzp, 1 + (z0 - own_lo),
+                                                 pads, S.comp);
+                if (e != CT_OK) return e;
+                CT_HIP(hipEventRecord(ev_up.e[1], S.comp));
+                staged = true;
+                return CT_OK;
+            };
+            for (int64_t h0 = own_lo; h0 < own_hi; h0 += nhost) {
+                const int64_t hn = std::min(nhost, own_hi - h0);
+                const char *from = (const char *)h_vol + h0 * slice;
+                if (!vol_pinned && whole) {
+                    if (used[q]) CT_HIP(hipEventSynchronize(ev_vol.e[q]));
+                    auto b = clk::now();
+                    par_memcpy(svol[q].p, from, (size_t)hn * slice);
+                    st.t_stage_s += secs(b, clk::now());
+                    from = (const char *)svol[q].p;
+                }
+                for (int64_t z0 = h0; z0 < h0 + hn; z0 += ZSTAGE) {
+                    const int64_t zn = std::min(ZSTAGE, h0 + hn - z0);
+                    if (staged) CT_HIP(hipStreamWaitEvent(S.h2d, ev_up.e[1], 0));  // the last piece has left the stage
+                    if (whole) {
+                        CT_HIP(hipMemcpyAsync(stage.p, from + (z0 - h0) * slice, zn * slice, hipMemcpyHostToDevice, S.h2d));
+                        st.bytes_h2d += (double)(zn * slice);
+                    } else if ((s = upload(stage.p, from, zn * slice)) != CT_OK) {
+                        return s;
+                    }
+                    if ((s = transpose(z0, zn)) != CT_OK) return s;
+                }
+                if (!vol_pinned && whole) {
+                    CT_HIP(hipEventRecord(ev_vol.e[q], S.h2d));
+                    used[q] = true;
+                    q ^= 1;
+                }
             }
+            CT_HIP(hipStreamSynchronize(S.h2d));  // the pinned buffers are free again
         } else {
             if ((s = upload(slab.p, (const char *)h_vol + mem_lo * slice, (mem_hi - mem_lo) * slice)) != CT_OK)
                 return s;
