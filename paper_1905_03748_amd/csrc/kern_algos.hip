@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 #include <utility>
 
 #include "dev_common.hpp"
@@ -185,13 +186,13 @@ __global__ __launch_bounds__(256) void k_sart_resid_t(const TP *__restrict__ b, 
 // of memory traffic per voxel and step, where a stored gradient took 24 (write g, read it for the norm,
 // read g and x, write x).  Each thread walks a run of slices of one (i, j) column: a voxel's gradient reads
 // seven positions of its own slice and three of the next, so the thread loads the seven positions of
-// each slice once and carries them up the column, with p_z of the slice below.  Positions past an
+// each slice once, a slice ahead of their use, and carries them up the column, with p_z of the slice below.  Positions past an
 // edge of the volume read the edge voxel, so their differences are zero without a test.  The
 // reciprocal square roots are the hardware's (1 ulp; a square root and a division each took about 25
 // instructions, four pairs per voxel): s >= eps, so a normal eps keeps them from denormal arguments, and
-// TINY serves an eps below FLT_MIN.  Bound: HBM and the address unit (7 loads of 4.7 cycles per wave and
+// TINY serves an eps below FLT_MIN (and slices of 2^32 pixels, with 64-bit offsets).  Bound: HBM and the address unit (7 loads of 4.7 cycles per wave and
 // slice) about evenly.
-// Five steps at 512^3 (with the copy of the image): 5.85 -> 2.90 ms.
+// Five steps at 512^3 (with the copy of the image): 5.85 -> 2.75 ms (2.90 before the loads ran ahead).
 constexpr int TV_TY = 8;               // rows of a tile (waves of a block); a tile is 64 columns wide
 constexpr int TV_THREADS = 64 * TV_TY;
 struct TvPlane {
@@ -203,44 +204,47 @@ struct TvArgs {
     int64_t kx0, kg0, nk;
     int zr;               // slices of a run
     unsigned bx, by, bz;  // tiles along each axis
+    int by_xcd;           // an eighth of the tiles, in order, per XCD
 };
+// Tile t in launch order (workgroups are dealt to the 8 XCDs in turn) as its place in the image.
+__device__ __forceinline__ unsigned tv_tile(const TvArgs &A, unsigned t) {
+    const unsigned e = A.bx * A.by * A.bz / 8;
+    return A.by_xcd && t < 8 * e ? (t % 8) * e + t / 8 : t;
+}
 template <bool TINY>
 __device__ __forceinline__ float tv_rsqrt(float s) {
     return TINY ? 1.0f / sqrtf(s) : __builtin_amdgcn_rsqf(s);
 }
 // visit(offset in x, x, g) for every voxel of the thread's run in the tile
 template <bool TINY, typename F>
-__device__ __forceinline__ void tv_walk(const float *__restrict__ x, const TvArgs &A, unsigned tx, unsigned ty,
-                                        unsigned tz, F visit) {
+__device__ __forceinline__ void tv_walk(const float *__restrict__ x, const TvArgs &A, unsigned t, F visit) {
+    const unsigned tx = t % A.bx, ty = t / A.bx % A.by, tz = t / (A.bx * A.by);
     const int i = (int)tx * 64 + ((int)threadIdx.x & 63);
     const int j = (int)ty * TV_TY + ((int)threadIdx.x >> 6);
     if (i >= A.nx || j >= A.ny) return;
     const int64_t sz = (int64_t)A.nx * A.ny;
-    const int oe = i < A.nx - 1 ? 1 : 0, ow = i > 0 ? -1 : 0;
-    const int on = j < A.ny - 1 ? A.nx : 0, os = j > 0 ? -A.nx : 0;
+    // offsets of the seven positions in a slice (32-bit from a wave-uniform slice base)
+    using O = typename std::conditional<TINY, int64_t, uint32_t>::type;
+    const O oc = (O)j * A.nx + i, oe = oc + (i < A.nx - 1 ? 1 : 0), ow = oc - (i > 0 ? 1 : 0);
+    const O up = j < A.ny - 1 ? A.nx : 0, dn = j > 0 ? A.nx : 0;
+    const O on = oc + up, own = ow + up, os = oc - dn, ose = oe - dn;
     const int64_t r0 = (int64_t)tz * A.zr, r1 = min(r0 + (int64_t)A.zr, A.nk);
     const int64_t k0 = A.kg0 + r0;
-    const float *p = x + (k0 - A.kx0) * sz + (int64_t)j * A.nx + i;
-    auto plane = [&](const float *q) {
-        TvPlane v;
-        v.c = q[0];
-        v.e = q[oe];
-        v.n = q[on];
-        v.w = q[ow];
-        v.wn = q[ow + on];
-        v.s = q[os];
-        v.se = q[os + oe];
-        return v;
-    };
-    TvPlane pc = plane(p);
+    const float *p = x + (k0 - A.kx0) * sz;  // slice of row r
+    auto plane = [&](const float *q) { return TvPlane{q[oc], q[oe], q[on], q[ow], q[own], q[os], q[ose]}; };
+    const int64_t top = min(r1, (int64_t)A.nz - 1 - A.kg0);  // rows below it have a slice above in the volume
+    TvPlane pc = plane(p), pn = r0 < top ? plane(p + sz) : pc;
     float pz = 0.0f;  // p_z of the slice below
     if (k0 > 0) {
         const float *q = p - sz;
-        const float c = q[0], dx = q[oe] - c, dy = q[on] - c, dz = pc.c - c;
+        const float c = q[oc], dx = q[oe] - c, dy = q[on] - c, dz = pc.c - c;
         pz = dz * tv_rsqrt<TINY>(fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, A.eps))));
     }
+#pragma unroll 1
     for (int64_t r = r0; r < r1; ++r, p += sz) {
-        const TvPlane pn = A.kg0 + r < A.nz - 1 ? plane(p + sz) : pc;
+        // the slice above the next one is loaded while this one is worked on
+        TvPlane pf = pn;
+        if (r + 1 < top) pf = plane(p + 2 * sz);
         const float c = pc.c;
         const float dx = pc.e - c, dy = pc.n - c, dz = pn.c - c;
         const float q = tv_rsqrt<TINY>(fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, A.eps))));
@@ -249,9 +253,10 @@ __device__ __forceinline__ void tv_walk(const float *__restrict__ x, const TvArg
         const float sx = pc.se - pc.s, sy = c - pc.s, sz_ = pn.s - pc.s;
         const float qs = tv_rsqrt<TINY>(fmaf(sx, sx, fmaf(sy, sy, fmaf(sz_, sz_, A.eps))));
         const float g = fmaf(-(dx + dy + dz), q, fmaf(wx, qw, fmaf(sy, qs, pz)));
-        visit(p - x, c, g);
+        visit((p - x) + oc, c, g);
         pz = dz * q;
         pc = pn;
+        pn = pf;
     }
 }
 
@@ -262,9 +267,9 @@ __global__ __launch_bounds__(TV_THREADS) void k_tv_norm(const float *__restrict_
                                                         double *__restrict__ partials) {
     __shared__ double lds[TV_TY];
     double gg = 0.0, xx = 0.0;
-    const unsigned per = A.bx * A.by, n = per * A.bz;
+    const unsigned n = A.bx * A.by * A.bz;
     for (unsigned t = blockIdx.x; t < n; t += gridDim.x)
-        tv_walk<TINY>(x, A, t % A.bx, t % per / A.bx, t / per, [&](int64_t o, float c, float g) {
+        tv_walk<TINY>(x, A, tv_tile(A, t), [&](int64_t o, float c, float g) {
             gg = fma((double)g, (double)g, gg);
             if (XX) xx = fma((double)c, (double)c, xx);
             if (COPY) y[o] = c;
@@ -308,7 +313,7 @@ __global__ __launch_bounds__(TV_THREADS) void k_tv_apply(const float *__restrict
     const bool go = ng2 > 0.0;
     const float a = go ? (float)(scal[1] / sqrt(ng2)) : 0.0f;
     float *yo = y - (ky0 - A.kx0) * ((int64_t)A.nx * A.ny);
-    tv_walk<TINY>(x, A, blockIdx.x, blockIdx.y, blockIdx.z,
+    tv_walk<TINY>(x, A, tv_tile(A, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x),
                   [&](int64_t o, float c, float g) { yo[o] = go ? fmaf(-a, g, c) : c; });
 }
 
@@ -329,20 +334,24 @@ TvArgs tv_args(int nx, int ny, int nz, double eps, int64_t kx0, int64_t kg0, int
     A.zr = 32;
     while (A.zr > 4 && (int64_t)A.bx * A.by * ((nk + A.zr - 1) / A.zr) < 1024) A.zr /= 2;
     A.bz = (unsigned)((nk + A.zr - 1) / A.zr);
+    // images that the 256 MB last-level cache holds: neighbouring tiles on one XCD read their shared rows
+    // from its L2 (256^3 0.39 -> 0.33 ms, 301 x 290 x 277 0.69 -> 0.64); larger ones stream better from all
+    // XCDs at once (512^3 2.74 against 2.82 ms)
+    A.by_xcd = (int64_t)nx * ny * nz <= (int64_t(64) << 20);
     return A;
 }
-bool tv_tiny(double eps) { return !((float)eps >= FLT_MIN); }
+bool tv_tiny(const TvArgs &A) { return !(A.eps >= FLT_MIN) || (int64_t)A.nx * A.ny >= (int64_t(1) << 32); }
 
 // ||g||^2 of slices kg0 .. kg0 + nk - 1 into scal[2]; xx: also their ||x||^2 into scal[0] and
 // alpha = lambda ||x|| into scal[1]; copy (with xx): x to y.  partials: 2 DOT_BLOCKS doubles.
-ct_status launch_tv_norm(const float *x, const TvArgs &A, double eps, bool xx, float *y, double *partials, double *scal,
-                         double lambda, hipStream_t st) {
+ct_status launch_tv_norm(const float *x, const TvArgs &A, bool xx, float *y, double *partials, double *scal, double lambda,
+                         hipStream_t st) {
     const int64_t tiles = (int64_t)A.bx * A.by * A.bz;
     if (tiles > 0x7fffffff) return fail(CT_ERR_ARG, "TV: the image is too large");
     const unsigned nb = (unsigned)std::min<int64_t>(tiles, DOT_BLOCKS);
 #define CT_TV_N(TI, XX_, CO) \
     hipLaunchKernelGGL((k_tv_norm<TI, XX_, CO>), dim3(nb), dim3(TV_THREADS), 0, st, x, A, y, partials)
-    if (tv_tiny(eps)) {
+    if (tv_tiny(A)) {
         if (xx && y) CT_TV_N(true, true, true);
         else if (xx) CT_TV_N(true, true, false);
         else CT_TV_N(true, false, false);
@@ -359,10 +368,9 @@ ct_status launch_tv_norm(const float *x, const TvArgs &A, double eps, bool xx, f
     return CT_OK;
 }
 
-ct_status launch_tv_apply(const float *x, float *y, const TvArgs &A, double eps, int64_t ky0, const double *scal,
-                          hipStream_t st) {
+ct_status launch_tv_apply(const float *x, float *y, const TvArgs &A, int64_t ky0, const double *scal, hipStream_t st) {
     const dim3 grid(A.bx, A.by, A.bz);
-    if (tv_tiny(eps)) hipLaunchKernelGGL((k_tv_apply<true>), grid, dim3(TV_THREADS), 0, st, x, y, A, ky0, scal);
+    if (tv_tiny(A)) hipLaunchKernelGGL((k_tv_apply<true>), grid, dim3(TV_THREADS), 0, st, x, y, A, ky0, scal);
     else hipLaunchKernelGGL((k_tv_apply<false>), grid, dim3(TV_THREADS), 0, st, x, y, A, ky0, scal);
     CT_HIP(hipGetLastError());
     return CT_OK;
@@ -769,9 +777,9 @@ ct_status tv_run(const ct_geometry &g, void *xs, ct_dtype vt, int32_t nsteps, do
     const bool copy = vt == CT_F32 && (nsteps & 1);
     float *src = copy ? buf : x, *dst = copy ? x : buf;
     for (int32_t k = 0; k < nsteps; ++k) {
-        if (k == 0) CK(launch_tv_norm(x, A, eps, true, copy ? buf : nullptr, parts, scal, lambda, st));
-        else CK(launch_tv_norm(src, A, eps, false, nullptr, parts, scal, lambda, st));
-        CK(launch_tv_apply(src, dst, A, eps, 0, scal, st));
+        if (k == 0) CK(launch_tv_norm(x, A, true, copy ? buf : nullptr, parts, scal, lambda, st));
+        else CK(launch_tv_norm(src, A, false, nullptr, parts, scal, lambda, st));
+        CK(launch_tv_apply(src, dst, A, 0, scal, st));
         std::swap(src, dst);
     }
     if (vt != CT_F32) CK(convert(src, CT_F32, xs, vt, nv, st));
@@ -928,7 +936,7 @@ ct_status tv_host_run(const ct_geometry &g, float *hx, int32_t nsteps, double la
     };
     // ||g||^2 (and, first step, ||x||^2) of the slab's own slices
     auto norms = [&](int64_t m0, int64_t o0, int64_t o1, bool with_x, double (&out)[3]) -> ct_status {
-        ct_status e = launch_tv_norm(xbuf, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), eps, with_x, nullptr,
+        ct_status e = launch_tv_norm(xbuf, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), with_x, nullptr,
                                      (double *)parts.p, dscal, lambda, s);
         if (e != CT_OK) return e;
         CT_HIP(hipMemcpyAsync(out, dscal, sizeof(out), hipMemcpyDeviceToHost, s));
@@ -966,7 +974,7 @@ ct_status tv_host_run(const ct_geometry &g, float *hx, int32_t nsteps, double la
             if (n + 1 < nsp)
                 CT_HIP(hipMemcpyAsync(saved.p, xbuf + (o1 - 1 - m0) * slice, (size_t)sb, hipMemcpyDeviceToDevice, s));
             const int64_t nown = (o1 - o0) * slice;
-            if ((e = launch_tv_apply(xbuf, gbuf, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), eps, o0, dscal, s)) !=
+            if ((e = launch_tv_apply(xbuf, gbuf, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), o0, dscal, s)) !=
                 CT_OK)
                 return e;
             CT_HIP(hipMemcpyAsync(hx + o0 * slice, gbuf, (size_t)nown * 4, hipMemcpyDeviceToHost, s));
@@ -1059,13 +1067,13 @@ ct_status tv_host_run_halo(const ct_geometry &g, float *hx, int32_t nsteps, doub
             float *cur = xbuf, *next = gbuf;
             for (int64_t i = 0; i < k; ++i) {
                 const int64_t r0 = m0 == 0 ? 0 : m0 + i + 1, r1 = m1 == nz ? nz : m1 - i - 1;
-                if ((e = launch_tv_norm(cur, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), eps, false, nullptr,
+                if ((e = launch_tv_norm(cur, tv_args(nx, ny, (int)nz, eps, m0, o0, o1 - o0), false, nullptr,
                                         (double *)parts.p, dscal, lambda, s)) != CT_OK)
                     return e;
                 hipLaunchKernelGGL(k_scale_entry, dim3(1), dim3(1), 0, s, dscal + 2, (double)nz / (double)(o1 - o0));
                 CT_HIP(hipGetLastError());
                 // the slices a later step still reads lie in [r0, r1)
-                if ((e = launch_tv_apply(cur, next, tv_args(nx, ny, (int)nz, eps, m0, r0, r1 - r0), eps, m0, dscal, s)) !=
+                if ((e = launch_tv_apply(cur, next, tv_args(nx, ny, (int)nz, eps, m0, r0, r1 - r0), m0, dscal, s)) !=
                     CT_OK)
                     return e;
                 std::swap(cur, next);
