@@ -97,6 +97,10 @@ struct Slab {
     bool scratch_ok;   // the launch may allocate device scratch (resident calls; not under a cap)
     bool zcol = false; // exact-adjoint backprojection only: the slab is column-major, [y][x][mem_n]
     bool no_alloc = false;  // the launch allocates nothing (the angle table must be on the device)
+    // exact-adjoint backprojection only: voxels may be taken in pairs, whose faces are rounded otherwise.  CGLS,
+    // whose recurrences carry 1e-10 of a difference in its first gradient to 1e-8 in its 64-bit residuals, takes
+    // each alone.
+    bool pairs = true;
 };
 
 inline Slab full_slab(const ct_geometry &g) {
@@ -213,9 +217,10 @@ ct_status ooc_plan(const ct_plan *p, int direction, ct_projector proj, ct_dtype 
 ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype vt, void *h_proj,
                       ct_dtype pt, uint64_t cap, ct_ooc_stats *stats);
 // fdk_filtered: the FDK reconstruction, each projection chunk weighted and ramp-filtered on the
-// device before its FDK-weighted backprojection (kind is then CT_BP_FDK)
+// device before its FDK-weighted backprojection (kind is then CT_BP_FDK); pairs: as in Slab
 ct_status ooc_backproject(ct_plan *p, ct_backprojector kind, const void *h_proj, ct_dtype pt, void *h_vol,
-                          ct_dtype vt, uint64_t cap, ct_ooc_stats *stats, bool fdk_filtered = false);
+                          ct_dtype vt, uint64_t cap, ct_ooc_stats *stats, bool fdk_filtered = false,
+                          bool pairs = true);
 
 // Out-of-core CGLS (ooc_cgls.cpp): host workspace r, q, s, p in FP32
 size_t cgls_host_workspace(const ct_plan *p);

@@ -621,6 +621,8 @@ ct_status cgls_run(ct_plan *p, const void *b, ct_dtype pt, void *x, ct_dtype vt,
     const size_t qbytes = (size_t)na * adj_chunk_bytes_per_angle(g);
     void *yq = ws.take(qbytes);
     const Slab full = full_slab(g);
+    Slab single = full;  // the adjoint's, voxels taken one by one
+    single.pairs = false;
     const bool col = zcol_ok(p, 0, na);
 #define CK(e)                          \
     do {                               \
@@ -639,7 +641,7 @@ ct_status cgls_run(ct_plan *p, const void *b, ct_dtype pt, void *x, ct_dtype vt,
     CK(fwd(x, vt, r));
     CT_DISPATCH1(pt, T, hipLaunchKernelGGL((k_rsub_from<T>), dim3(ew_grid(np)), dim3(EW_THREADS), 0, st, (const T *)b, r, np));
     CT_HIP(hipGetLastError());
-    CK(launch_backproject(p, CT_BP_ADJOINT, r, CT_F32, sv, CT_F32, 0, 0, na, full, st, yq, qbytes));
+    CK(launch_backproject(p, CT_BP_ADJOINT, r, CT_F32, sv, CT_F32, 0, 0, na, single, st, yq, qbytes));
     hipLaunchKernelGGL((k_copy<float>), dim3(ew_grid(nv)), dim3(EW_THREADS), 0, st, (const float *)sv, pv, nv);
     CT_HIP(hipGetLastError());
     CK(dot_f64(sv, sv, CT_F32, nv, scal + S_GAMMA, parts, st));
@@ -659,7 +661,7 @@ ct_status cgls_run(ct_plan *p, const void *b, ct_dtype pt, void *x, ct_dtype vt,
                            (int)S_ALPHA, -1.0f, np);
         CT_HIP(hipGetLastError());
         // s = A^T r ; gamma' = <s,s> ; beta = gamma'/gamma ; p = s + beta p
-        CK(launch_backproject(p, CT_BP_ADJOINT, r, CT_F32, sv, CT_F32, 0, 0, na, full, st, yq, qbytes));
+        CK(launch_backproject(p, CT_BP_ADJOINT, r, CT_F32, sv, CT_F32, 0, 0, na, single, st, yq, qbytes));
         CK(dot_f64(sv, sv, CT_F32, nv, scal + S_TMP, parts, st));
         hipLaunchKernelGGL(k_cgls_beta, dim3(1), dim3(1), 0, st, scal);
         CT_HIP(hipGetLastError());

@@ -534,7 +534,7 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
 }
 
 ct_status ooc_backproject(ct_plan *p, ct_backprojector kind, const void *h_proj, ct_dtype pt, void *h_vol, ct_dtype vt,
-                          uint64_t cap, ct_ooc_stats *stats, bool fdk_filtered) {
+                          uint64_t cap, ct_ooc_stats *stats, bool fdk_filtered, bool pairs) {
     const auto t_start = clk::now();
     const ct_geometry &g = p->g;
     Layout L;
@@ -716,6 +716,7 @@ ct_status ooc_backproject(ct_plan *p, ct_backprojector kind, const void *h_proj,
         sl.first = sl.last = true;
         sl.scratch_ok = false;
         sl.zcol = zcol;
+        sl.pairs = pairs;
         // the detector rows the slab's voxels read (bilinear taps, or the rays that cross their
         // boxes, with two rows to spare for the candidate rows the exact adjoint visits); the rest of
         // each chunk buffer is zeroed once per slab and never sent

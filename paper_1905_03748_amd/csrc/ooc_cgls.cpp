@@ -179,7 +179,7 @@ ct_status cgls_host_run(ct_plan *p, const float *b, float *x, int32_t niter, dou
     };
     auto adj = [&](const float *y, float *out) -> ct_status {
         ct_ooc_stats st;
-        ct_status e = ooc_backproject(p, CT_BP_ADJOINT, y, CT_F32, out, CT_F32, cap, &st);
+        ct_status e = ooc_backproject(p, CT_BP_ADJOINT, y, CT_F32, out, CT_F32, cap, &st, false, false);
         if (e != CT_OK) return e;
         add_stats(tot, st);
         return CT_OK;
