@@ -599,7 +599,7 @@ def main():
                 "siddon_fwd_gvps": round(vp / (fwd_ms * 1e-3) / 1e9, 2),
                 "fdk_bp_gvps": round(vp / (bp_ms * 1e-3) / 1e9, 2)},
         "roofline": {"bound": "hbm",
-                     "kernel": "k_siddon_col<float, float, 2>" if dom == "siddon" else "k_bp_lds<0, 37, float, float>",
+                     "kernel": "k_siddon_pair<float, float>" if dom == "siddon" else "k_bp_lds<0, 37, float, float>",
                      "byte_model": "gather model: %s B per voxel.proj x %.4g voxel.proj per launch"
                                    % (round(BYTES_PER_VP[dom], 3), vp),
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -186,12 +186,12 @@ __global__ __launch_bounds__(256) void k_sart_resid_t(const TP *__restrict__ b, 
 // of memory traffic per voxel and step, where a stored gradient took 24 (write g, read it for the norm,
 // read g and x, write x).  Each thread walks a run of slices of one (i, j) column: a voxel's gradient reads
 // seven positions of its own slice and three of the next, so the thread loads the seven positions of
-// each slice once, a slice ahead of their use, and carries them up the column, with p_z of the slice below.  Positions past an
-// edge of the volume read the edge voxel, so their differences are zero without a test.  The
-// reciprocal square roots are the hardware's (1 ulp; a square root and a division each took about 25
+// each slice once, a slice ahead of their use, and carries them up the column, with p_z of the slice below.
+// Positions past an edge of the volume read the edge voxel, so their differences are zero without a test.
+// The reciprocal square roots are the hardware's (1 ulp; a square root and a division each took about 25
 // instructions, four pairs per voxel): s >= eps, so a normal eps keeps them from denormal arguments, and
-// TINY serves an eps below FLT_MIN (and slices of 2^32 pixels, with 64-bit offsets).  Bound: HBM and the address unit (7 loads of 4.7 cycles per wave and
-// slice) about evenly.
+// TINY serves an eps below FLT_MIN (and slices of 2^32 pixels, with 64-bit offsets).  Bound: HBM and the
+// address unit (7 loads of 4.7 cycles per wave and slice) about evenly.
 // Five steps at 512^3 (with the copy of the image): 5.85 -> 2.75 ms (2.90 before the loads ran ahead).
 constexpr int TV_TY = 8;               // rows of a tile (waves of a block); a tile is 64 columns wide
 constexpr int TV_THREADS = 64 * TV_TY;

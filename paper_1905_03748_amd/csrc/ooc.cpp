@@ -34,6 +34,11 @@ constexpr size_t STAGE_PIECE = 64ull << 20;    // slab staging piece
 // pageable slabs are sent in pieces of this size where they can: each first write to a page of a new
 // pinned buffer faults it in (512^3: pieces of 16 / 32 / 64 MiB 29.4 / 30.8 / 33 ms)
 constexpr size_t UPLOAD_PIECE = 16ull << 20;
+// Pageable volumes below this size go up ZSTAGE slices at a time through one reused buffer, whose few pages
+// are soon faulted in, the host waiting for each: faults and events cost more there than overlap saves (97^3:
+// 2.2 against 3.5 ms with the larger pieces, 263 x 209 x 235, 52 MB: 8.3 against 9.2, but 328 x 283 x 323,
+// 120 MB: 15.0 against 12.4).
+constexpr size_t UPLOAD_SMALL = 80ull << 20;
 
 using clk = std::chrono::steady_clock;
 double secs(clk::time_point a, clk::time_point b) { return std::chrono::duration<double>(b - a).count(); }
@@ -390,23 +395,31 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
             // The stage passes between the copy stream and the compute stream by events, and a pageable
             // volume is copied into one pinned buffer, as many slices at a time as it holds, while the
             // other is sent, so the host waits for a buffer only (512^3 in two slabs, 60 angles: 62 ->
-            // 29 ms with the rows' copies on threads too; the host copied 8 slices on one thread, waited for them and for their transpose).
+            // 29 ms with the rows' copies on threads too, where one thread copied 8 slices, then the host
+            // waited for them and for their transpose).
             const int64_t nzp = (own_hi - own_lo) + 2;
             const size_t piece = std::max<size_t>(UPLOAD_PIECE, (size_t)ZSTAGE * slice);
-            const int64_t fit = piece <= STAGE_PIECE ? (int64_t)(piece / slice) / ZSTAGE * ZSTAGE : 0;
+            const bool small = (size_t)g.nVoxel[2] * slice < UPLOAD_SMALL;
+            const int64_t fit = piece <= STAGE_PIECE && !small ? (int64_t)(piece / slice) / ZSTAGE * ZSTAGE : 0;
             const bool whole = vol_pinned || fit > 0;  // a pinned buffer holds a piece
             const int64_t nhost = vol_pinned ? own_hi - own_lo : std::max(fit, ZSTAGE);
             bool used[2] = {false, false}, staged = false;
             int q = 0;
             auto transpose = [&](int64_t z0, int64_t zn) -> ct_status {
-                CT_HIP(hipEventRecord(ev_up.e[0], S.h2d));
-                CT_HIP(hipStreamWaitEvent(S.comp, ev_up.e[0], 0));
+                if (whole) {
+                    CT_HIP(hipEventRecord(ev_up.e[0], S.h2d));
+                    CT_HIP(hipStreamWaitEvent(S.comp, ev_up.e[0], 0));
+                }
                 const int pads = (z0 == own_lo ? 1 : 0) | (z0 + zn == own_hi ? 2 : 0);
                 ct_status e = launch_zcols_piece(stage.p, vt, cols, g.nVoxel[0], g.nVoxel[1], zn, nzp, 1 + (z0 - own_lo),
                                                  pads, S.comp);
                 if (e != CT_OK) return e;
-                CT_HIP(hipEventRecord(ev_up.e[1], S.comp));
-                staged = true;
+                if (whole) {
+                    CT_HIP(hipEventRecord(ev_up.e[1], S.comp));
+                    staged = true;
+                } else {
+                    CT_HIP(hipStreamSynchronize(S.comp));  // upload() has waited for the piece; the stage is free again
+                }
                 return CT_OK;
             };
             for (int64_t h0 = own_lo; h0 < own_hi; h0 += nhost) {
