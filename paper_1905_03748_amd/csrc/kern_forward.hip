@@ -1111,7 +1111,7 @@ __global__ __launch_bounds__(256) void k_pcols2(const TV *__restrict__ src, TV *
 #endif
 
 // The kernel is bound by VALU issue as much as by its loads, and most of its instructions form indices.
-// C32 (x-paired copies below 4 GiB): a cell's offset is two 24-bit multiply-adds of the floors relative to the
+// C32 (x-paired copies below 1 GiB): a cell's offset is two 24-bit multiply-adds of the floors relative to the
 // ray's first voxel plus that voxel's offset, all in 32 bits; with one sample per trip the sample index is
 // the same for all lanes, and lanes past their last sample run on outside the grid and add nothing (rows of
 // tilted columns end far apart, and those run on through the volume: 9.3 against 8.9 ms).  Indices are not clamped per
@@ -1678,7 +1678,10 @@ ct_status launch_forward(ct_plan *p, ct_projector kind, const void *vol, ct_dtyp
 #endif
         const bool xp = 2 * pbytes <= CT_IC_XPAIR_MAX;
         // cell offsets in 32 bits: the paired copy below 4 GiB, a padded slice within the 24-bit multiply
-        const bool c32 = xp && 2 * pbytes < (size_t(1) << 32) && (nx + 3) * (nz + 3) < (1 << 23);
+        // 32-bit cells up to 1 GiB: larger copies are bound by what leaves L2, and lanes running on past their
+        // last sample add to it (FP32, 448^3 / 200 angles, 0.73 GB: 43.8 -> 40.1 ms; 512^3 / 360, 1.09 GB:
+        // 107 -> 111 ms; FP16 512^3 / 180, 0.55 GB: 57 -> 48 ms)
+        const bool c32 = xp && 2 * pbytes < (size_t(1) << 30) && (nx + 3) * (nz + 3) < (1 << 23);
         void *vpad = nullptr;
         if (CT_MALLOC_ASYNC(&vpad, xp ? 2 * pbytes : pbytes, st) == hipSuccess) {
             const dim3 tg((unsigned)((nx + 3 + 31) / 32), (unsigned)((nz + 3 + 31) / 32), (unsigned)(ny + 3));
