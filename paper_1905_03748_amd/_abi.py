@@ -80,6 +80,7 @@ SIGNATURES = {
     "ct_tv_steps_host": [C.POINTER(ct_geometry), _P, _I32, _D, _D, _I32, _U64, C.POINTER(ct_ooc_stats)],
     "ct_rof_workspace_bytes": [C.POINTER(ct_geometry), C.POINTER(_U64)],
     "ct_rof": [C.POINTER(ct_geometry), _P, _I32, _D, _D, _P, _P],
+    "ct_rof_sized": [C.POINTER(ct_geometry), _P, _I32, _D, _D, _P, _U64, _P],
     "ct_rof_host_workspace_bytes": [C.POINTER(ct_geometry), C.POINTER(_U64)],
     "ct_rof_host": [C.POINTER(ct_geometry), _P, _I32, _D, _D, _I32, _P, _U64, C.POINTER(ct_ooc_stats)],
     "ct_dot": [_P, _P, _INT, _I64, _P, _P],
@@ -275,6 +276,11 @@ def ct_rof_workspace_bytes(geometry: ct_geometry) -> int:
 def ct_rof(geometry: ct_geometry, d_x, niter, lam, tau, d_workspace=0, stream=0):
     return _check(lib().ct_rof(C.byref(geometry), d_x, niter, float(lam), float(tau), d_workspace or None,
                                stream or None))
+
+
+def ct_rof_sized(geometry: ct_geometry, d_x, niter, lam, tau, d_workspace=0, workspace_bytes=0, stream=0):
+    return _check(lib().ct_rof_sized(C.byref(geometry), d_x, niter, float(lam), float(tau), d_workspace or None,
+                                     int(workspace_bytes), stream or None))
 
 
 def ct_rof_host_workspace_bytes(geometry: ct_geometry) -> int:

@@ -488,6 +488,12 @@ ct_status ct_rof_workspace_bytes(const ct_geometry *geometry, uint64_t *bytes) {
 
 ct_status ct_rof(const ct_geometry *geometry, void *d_x, int32_t niter, double lambda, double tau, void *d_workspace,
                  void *stream) {
+    // a buffer of unknown size holds the volumes that ct_rof_workspace_bytes asks for and no more
+    return ct_rof_sized(geometry, d_x, niter, lambda, tau, d_workspace, geometry ? rof_workspace(*geometry) : 0, stream);
+}
+
+ct_status ct_rof_sized(const ct_geometry *geometry, void *d_x, int32_t niter, double lambda, double tau,
+                       void *d_workspace, uint64_t workspace_bytes, void *stream) {
     if (!geometry || !d_x) return fail(CT_ERR_ARG, "ct_rof: null pointer");
     if (niter < 0) return fail(CT_ERR_ARG, "ct_rof: niter must be >= 0");
     if (!(lambda > 0) || !std::isfinite(lambda) || !(tau > 0) || !std::isfinite(tau))
@@ -495,7 +501,9 @@ ct_status ct_rof(const ct_geometry *geometry, void *d_x, int32_t niter, double l
     for (int a = 0; a < 3; ++a)
         if (geometry->nVoxel[a] <= 0) return fail(CT_ERR_GEOMETRY, "ct_rof: voxel counts must be positive");
     if (geometry->nVoxel[2] > 65535) return fail(CT_ERR_ARG, "ct_rof: more than 65535 slices");
-    return rof_run(*geometry, d_x, niter, lambda, tau, d_workspace, (hipStream_t)stream);
+    if (d_workspace && workspace_bytes < rof_workspace(*geometry))
+        return fail(CT_ERR_ARG, "ct_rof: the workspace is smaller than ct_rof_workspace_bytes");
+    return rof_run(*geometry, d_x, niter, lambda, tau, d_workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 ct_status ct_rof_host_workspace_bytes(const ct_geometry *geometry, uint64_t *bytes) {

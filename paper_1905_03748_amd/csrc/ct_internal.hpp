@@ -178,7 +178,9 @@ size_t sart_workspace(const ct_plan *p, int32_t block);
 ct_status tv_run(const ct_geometry &g, void *x, ct_dtype vt, int32_t nsteps, double lambda, double eps, void *work,
                  hipStream_t st);
 size_t tv_workspace(const ct_geometry &g, ct_dtype vt);
-ct_status rof_run(const ct_geometry &g, void *x, int32_t niter, double lambda, double tau, void *work, hipStream_t st);
+// work: NULL or a buffer of work_bytes bytes, at least rof_workspace
+ct_status rof_run(const ct_geometry &g, void *x, int32_t niter, double lambda, double tau, void *work, size_t work_bytes,
+                  hipStream_t st);
 size_t rof_workspace(const ct_geometry &g);
 // the same on a host image; hp: host workspace of rof_host_workspace bytes (the dual field)
 ct_status rof_host_run(const ct_geometry &g, float *hx, int32_t niter, double lambda, double tau, int32_t depth,

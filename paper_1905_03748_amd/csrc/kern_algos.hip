@@ -797,7 +797,7 @@ namespace {
 // Whether an iteration runs in one pass between two dual fields (workspace: six volumes) or in two
 // passes over one (four: px, py, pz, w).  The one-pass form takes half the time; above 16 GiB per volume
 // its two more volumes would be what no longer fits a 288 GB device, so the four-volume form stays there,
-// and where the library's own allocation of six fails.
+// where the library's own allocation of six fails, and for callers' buffers that hold four.
 bool rof_one_pass(const ct_geometry &g) {
     return (uint64_t)g.nVoxel[0] * g.nVoxel[1] * g.nVoxel[2] <= (uint64_t(4) << 30);
 }
@@ -806,15 +806,16 @@ size_t rof_volumes(const ct_geometry &g, int n) {
 }
 }  // namespace
 
-size_t rof_workspace(const ct_geometry &g) { return rof_volumes(g, rof_one_pass(g) ? 6 : 4); }
+size_t rof_workspace(const ct_geometry &g) { return rof_volumes(g, 4); }
 
-ct_status rof_run(const ct_geometry &g, void *x, int32_t niter, double lambda, double tau, void *work, hipStream_t st) {
+ct_status rof_run(const ct_geometry &g, void *x, int32_t niter, double lambda, double tau, void *work, size_t work_bytes,
+                  hipStream_t st) {
     const int nx = (int)g.nVoxel[0], ny = (int)g.nVoxel[1], nz = (int)g.nVoxel[2];
     const int64_t nv = (int64_t)nx * ny * nz;
     if (niter == 0) return CT_OK;  // u = f
-    bool one = rof_one_pass(g);
+    bool one = rof_one_pass(g) && (!work || work_bytes >= rof_volumes(g, 6));
     Workspace ws;
-    ct_status s = ws.acquire(work, rof_workspace(g), st);
+    ct_status s = ws.acquire(work, rof_volumes(g, one ? 6 : 4), st);
     if (s == CT_ERR_OOM && one) {
         (void)hipGetLastError();
         one = false;

@@ -268,14 +268,18 @@ def tv_steps_host(geometry: dict, x: torch.Tensor, nsteps: int, lam: float, eps:
 
 def rof(geometry: dict, x: torch.Tensor, niter: int, lam: float, tau: float = 1.0 / 12.0, workspace=None,
         stream=None) -> torch.Tensor:
-    """ROF denoising in place on the FP32 device volume x (Chambolle's projection, niter iterations)."""
+    """ROF denoising in place on the FP32 device volume x (Chambolle's projection, niter iterations).
+    workspace: a contiguous device tensor of rof_workspace_bytes bytes, or of four volumes (_abi's
+    ct_rof_workspace_bytes) at the least: the iterations then take two passes each, with the same
+    result.  None: the library allocates what it can of the two."""
     nx, ny, nz = (int(v) for v in geometry["nVoxel"])
     if x.dtype != torch.float32:
         raise TypeError("rof works on FP32 volumes")
+    g = A.make_geometry(geometry)
     if workspace is not None:
-        _check_workspace(workspace, rof_workspace_bytes(geometry))
-    A.ct_rof(A.make_geometry(geometry), _dev(x, (nz, ny, nx), "x"), niter, lam, tau,
-             workspace.data_ptr() if workspace is not None else 0, _stream(stream))
+        _check_workspace(workspace, A.ct_rof_workspace_bytes(g))
+    A.ct_rof_sized(g, _dev(x, (nz, ny, nx), "x"), niter, lam, tau, workspace.data_ptr() if workspace is not None else 0,
+                   workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(stream))
     return x
 
 
@@ -296,7 +300,10 @@ def rof_host(geometry: dict, x: torch.Tensor, niter: int, lam: float, tau: float
 
 
 def rof_workspace_bytes(geometry: dict) -> int:
-    return A.ct_rof_workspace_bytes(A.make_geometry(geometry))
+    """The workspace with which rof runs each iteration in one pass: six volumes (four, the least that rof
+    takes, for volumes above 16 GiB, where it always makes two)."""
+    least = A.ct_rof_workspace_bytes(A.make_geometry(geometry))
+    return least // 2 * 3 if least <= 4 * (16 << 30) else least
 
 
 def tv_workspace_bytes(geometry: dict, dtype=torch.float32) -> int:
