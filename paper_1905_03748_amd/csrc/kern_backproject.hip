@@ -802,10 +802,11 @@ __global__ __launch_bounds__(256) CT_ADJ_OCC void k_adj_col(const float *__restr
                   : ((int64_t)(k - A.mem_lo) * A.ny + j) * A.nx + i;
     };
     static_assert(!PAIR || (R % 2 == 0 && !ORD), "pairs take the general face order");
+    // first voxel of the wave's lanes; pairs are (2 m, 2 m + 1) by the volume's own slices, so that a voxel's
+    // rounding does not depend on where a slab starts (a pair's half outside the slab is not kept)
+    const int kw0 = (PAIR ? A.own_lo & ~1 : A.own_lo) + zg * 64 * R;
     // slice of the lane's voxel r
-    auto slice_of = [&](int r) {
-        return A.own_lo + zg * 64 * R + (PAIR ? 128 * (r / 2) + 2 * lane + r % 2 : 64 * r + lane);
-    };
+    auto slice_of = [&](int r) { return kw0 + (PAIR ? 128 * (r / 2) + 2 * lane + r % 2 : 64 * r + lane); };
     // za, zb: the voxel's faces in the order its rows reach them (lower face first unless ORD and
     // the voxel lies below the source plane), for choosing the candidate rows.
     // kA, sg: index of the face that rows of the voxel's side of the source plane reach first (the
@@ -816,7 +817,7 @@ __global__ __launch_bounds__(256) CT_ADJ_OCC void k_adj_col(const float *__restr
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int k = slice_of(r);
-        kin[r] = k < A.own_hi;
+        kin[r] = (!PAIR || k >= A.own_lo) && k < A.own_hi;
         const float zl = fmaf((float)k, dz, zface0), zh = fmaf((float)(k + 1), dz, zface0);
         if (VW || PAIR) {
             // the faces in the world frame; each view takes them relative to its source
@@ -854,7 +855,6 @@ __global__ __launch_bounds__(256) CT_ADJ_OCC void k_adj_col(const float *__restr
     // that angle's candidate columns, a prefix sum over the wave lays the (angle, column) pairs out
     // in angle order, each lane forms the set-up of one pair into LDS, and the voxel loop reads the
     // pairs back in that order (the same sums in the same order as one pair after another).
-    const int kw0 = A.own_lo + zg * 64 * R;  // first voxel of the wave's lanes
     float4(*hdr)[3] = chdr[wave];
     int(*slot)[64] = cslot[wave];
     int tprev = -1;
@@ -1659,7 +1659,15 @@ ct_status launch_backproject(ct_plan *p, ct_backprojector kind, const void *proj
         }
         if (nr <= 4 && yq && qcap >= per_angle) {
             const int64_t kq = std::min<int64_t>(a1 - a0, (int64_t)(qcap / per_angle));
-            int R = lane_voxels(nzown);
+            // Pairs of voxels where the rows that can meet two fit one 16-byte load, unless the caller's sums are
+            // to be those of voxels taken one by one (CGLS on 243 x 251 x 187: 24.0 against 19.4 ms).  The choice
+            // does not look at the slab, so a volume cut into slabs gets the bits of the whole one: pairs serve
+            // up to 64 slices too, with half of their lanes (64 slices of 256^2 / 30 angles, 2 / 3 / 4 rows
+            // meeting a pair: 183 / 208 / 265 us, one by one with all lanes 256 / 262 / 301).
+            const int nr2 = std::min<int>(p->views ? adj_rows_views(p, 2) : adj_rows(p->g, 2), (int)p->g.nDetector[1] + 2);
+            const bool pairs = slab.pairs && nr2 <= 4;
+            const int64_t nzspan = slab.own_hi - (pairs ? slab.own_lo & ~int64_t(1) : slab.own_lo);
+            int R = std::max(lane_voxels(nzspan), pairs ? 2 : 1);
 #ifdef CT_ADJ_R
             R = CT_ADJ_R;
 #endif
@@ -1671,7 +1679,7 @@ ct_status launch_backproject(ct_plan *p, ct_backprojector kind, const void *proj
                 for (int64_t k = slab.own_lo; k < slab.own_hi && ord; ++k)
                     ord = !(std::fma((float)k, dzf, zf0) < 0.0f && std::fma((float)(k + 1), dzf, zf0) > 0.0f);
             }
-            const int zgroups = (int)((nzown + 64 * R - 1) / (64 * R));
+            const int zgroups = (int)((nzspan + 64 * R - 1) / (64 * R));
             const int xblocks = (A.nx + 3) / 4;
             const dim3 ag((unsigned)((int64_t)zgroups * xblocks * A.ny));
             const size_t pangle = (size_t)A.nu * A.nv * dtype_size(pt);
@@ -1684,10 +1692,7 @@ ct_status launch_backproject(ct_plan *p, ct_backprojector kind, const void *proj
                 CT_DISPATCH1(pt, TP,
                              hipLaunchKernelGGL((k_adj_prep<TP>), pg, dim3(256), 0, st, (const TP *)pc, (float *)yq, Ac));
                 CT_HIP(hipGetLastError());
-                // pairs of voxels where the rows that can meet two fit one 16-byte load, unless the caller's sums
-                // are to be those of voxels taken one by one (CGLS on 243 x 251 x 187: 24.0 against 19.4 ms)
-                const int nr2 = std::min<int>(p->views ? adj_rows_views(p, 2) : adj_rows(p->g, 2), (int)p->g.nDetector[1] + 2);
-                if (R % 2 == 0 && nr2 <= 4 && slab.pairs) {
+                if (pairs) {
 #define CT_ADJ_P(RR, NN)                                                                                          \
     CT_DISPATCH1(vt, TV, if (p->views) {                                                                          \
         hipLaunchKernelGGL((k_adj_col<TV, RR, NN, false, false, true, true>), ag, block, rsbytes, st,             \
