@@ -101,6 +101,9 @@ struct Slab {
     // whose recurrences carry 1e-10 of a difference in its first gradient to 1e-8 in its 64-bit residuals, takes
     // each alone.
     bool pairs = true;
+    // Siddon only: the walk is chosen for the launch's own angles; else for the plan's, so that any range of them
+    // gives the bits of the whole
+    bool own_angles = false;
 };
 
 inline Slab full_slab(const ct_geometry &g) {

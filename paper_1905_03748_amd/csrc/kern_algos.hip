@@ -704,7 +704,8 @@ ct_status sart_run(ct_plan *p, const void *b, ct_dtype pt, void *x, ct_dtype vt,
     const float thr = (float)(1e-2 * std::fmin(g.dVoxel[0], std::fmin(g.dVoxel[1], g.dVoxel[2])));
     const int nu = (int)g.nDetector[0], nv = (int)g.nDetector[1];
     CK(launch_ray_chord(p, chord, 0, na, st));
-    const Slab full = full_slab(g);
+    Slab full = full_slab(g);
+    full.own_angles = true;  // (a sweep always projects the same subsets)
     // the sweep updates an FP32 image: the column-major copy, or (other geometries) x itself when
     // it is stored in FP32, else an FP32 copy of it; a 16-bit x is rounded once, at the end
     // the column-major sweep's update kernel is written for a circular orbit; plans of views update

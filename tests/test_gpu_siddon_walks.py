@@ -1,0 +1,86 @@
+"""Which walk the column Siddon projector takes: neighbouring rows in pairs for plans that fill the chip, rows
+64 apart for smaller ones, chosen by the plan so that a range of its angles gives the bits of the whole.  The
+pair walk against the CPU FP64 oracle on plans of that size."""
+import numpy as np
+import pytest
+import torch
+
+from _helpers import TOL_PROJ, rel_l2, say
+from paper_1905_03748_amd import inputs
+from paper_1905_03748_amd.operators import Plan
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _work(nv, dv, offv, nz=40, views=150, nu=33):
+    return inputs.Workload("walks", (41, 38, nz), (1.0, 1.1, 1.0), (nu, nv), (69.3 / nu, dv), views, 10, 3,
+                           off_origin=(2.0, -1.0, 0.7), off_detector=(0.31, offv))
+
+
+def _volume(w):
+    return np.random.default_rng(5).uniform(0, 1, w.nvox[::-1]).astype(np.float32)
+
+
+# rows, row pitch (mm), detector offset (mm), slices: with 1 mm slices the rows lie 0.56 .. 0.78 of the pitch
+# apart in the grid; 9 blocks a view and 128 rows, 1350 and more in all
+@pytest.mark.parametrize("nv,dv,offv,nz", [
+    (72, 1.1, 0.0, 40), (73, 1.6, 0.3, 40), (127, 1.6, 0.0, 40), (128, 1.6, 0.4, 40), (129, 1.6, -0.2, 40),
+    (130, 2.2, 0.0, 40), (257, 0.7, 0.1, 40), (90, 2.9, 0.0, 40), (78, 1.6, 90.0, 40), (78, 1.6, -90.0, 40),
+    (200, 2.4, 20.0, 40), (75, 1.5, 0.0, 1), (75, 1.5, 0.0, 2), (75, 2.2, 0.0, 3)])
+def test_pair_walk_matches_the_oracle(orc, nv, dv, offv, nz):
+    w = _work(nv, dv, offv, nz)
+    vol = _volume(w)
+    x = torch.from_numpy(vol).to(DEV)
+    og = orc.Geometry.from_dict(w.geometry_dict())
+    for scan in (w.angles, inputs.helical_views(w.DSO, w.DSD, w.angles, pitch=12.0, z0=-6.0)):
+        say(f"[siddon walks] {nv} rows of {dv} mm, offset {offv}, {nz} slices, {np.ndim(scan)}-d scan")
+        ref = orc.siddon_fwd(og, scan, vol.astype(np.float64))
+        plan = Plan(w.geometry_dict(), scan)
+        got = plan.forward(x, "siddon")
+        assert rel_l2(got.cpu().numpy(), ref) <= TOL_PROJ
+        out = plan.forward(x, "siddon", angle_begin=3, angle_end=11)
+        assert torch.equal(out, got[3:11])
+        plan.forward(x, "siddon", out=out, accumulate=True, angle_begin=3, angle_end=11)
+        assert rel_l2(out.cpu().numpy(), 2.0 * ref[3:11]) <= TOL_PROJ
+        h = x.half()
+        assert rel_l2(plan.forward(h, "siddon", out_dtype=torch.float32).cpu().numpy(),
+                      plan.forward(h.float(), "siddon").cpu().numpy()) <= 1e-6
+
+
+@pytest.mark.parametrize("at", [(1, 0, 0), (20, 19, 20), (38, 37, 40)])
+@pytest.mark.parametrize("dv", [1.1, 1.6, 2.4])
+def test_pair_walk_non_finite_voxel(orc, at, dv):
+    w = _work(129, dv, 0.0, views=70)   # 1260 blocks
+    vol = _volume(w)
+    near = np.zeros(w.nvox[::-1])
+    near[max(at[0] - 1, 0):at[0] + 2, at[1], at[2]] = 1.0
+    og = orc.Geometry.from_dict(w.geometry_dict())
+    reach = orc.siddon_fwd(og, w.angles, near) > 0
+    through = np.zeros_like(near)
+    through[at] = 1.0
+    hit = orc.siddon_fwd(og, w.angles, through) > 1e-3
+    vol[at] = np.nan
+    say(f"[siddon walks] NaN at {at}, rows of {dv} mm")
+    p = Plan(w.geometry_dict(), w.angles).forward(torch.from_numpy(vol).to(DEV), "siddon").cpu().numpy()
+    assert np.all(np.isnan(p[hit])) and not np.any(np.isnan(p[~reach]))
+
+
+@pytest.mark.parametrize("dt,nv,views,pairs", [
+    (torch.float32, 130, 4, False), (torch.float32, 130, 56, False), (torch.float32, 130, 57, True),
+    (torch.float16, 130, 71, False), (torch.float16, 130, 72, True),
+    (torch.float32, 71, 300, False), (torch.float32, 72, 300, True)])
+def test_walk_is_chosen_by_the_plan(dt, nv, views, pairs):
+    # the first two views of a small and of a large plan are the same rays: the pair walk adds the pieces of a
+    # ray in another order, so the two walks differ in their last bits
+    w = _work(nv, 1.6, 0.4)
+    geo = w.geometry_dict()
+    x = torch.from_numpy(_volume(w)).to(DEV).to(dt)
+    angles = np.concatenate([[0.1, 0.9], np.linspace(0.2, 6.0, views - 2)])
+    say(f"[siddon walks] {nv} rows, {views} views, {dt}")
+    plan = Plan(geo, angles)
+    head = plan.forward(x, "siddon", angle_begin=0, angle_end=2, out_dtype=torch.float32)
+    assert torch.equal(plan.forward(x, "siddon", out_dtype=torch.float32)[:2], head)
+    small = Plan(geo, angles[:2]).forward(x, "siddon", out_dtype=torch.float32)
+    assert rel_l2(head.cpu().numpy(), small.cpu().numpy()) <= 1e-6
+    assert torch.equal(head, small) == (not pairs)
