@@ -211,8 +211,6 @@ ct_status launch_ray_chord(ct_plan *p, float *chord, int64_t a0, int64_t a1, hip
 ct_status launch_sart_update(ct_plan *p, const float *r, float *vol, int64_t a0, int64_t a1, float lambda,
                              hipStream_t st);
 // the same update on the column-major copy (launch_zcols layout), residuals rT in [a1-a0][u][v] layout
-// (sart_col_ok: the rows that one wave's heights meet fit its LDS)
-bool sart_col_ok(const ct_plan *p);
 ct_status launch_sart_update_col(ct_plan *p, const float *rT, float *vz, int64_t a0, int64_t a1, float lambda,
                                  hipStream_t st);
 

@@ -1565,7 +1565,6 @@ BpArgs make_bp_args(ct_plan *p, const AngleGeo *tab, int64_t a0, int64_t a1, con
 
 // Detector rows that 64 R heights of a voxel column can meet, at most, with the second tap and a margin: a
 // height step is dz m / dv rows, the magnification m at most DSD / (DSO - R').
-constexpr int64_t SART_MAX_ROWS = 2048;  // 32 KiB of LDS per block
 int64_t sart_rows(const ct_geometry &g, int R) {
     double rad = 0.0;
     for (int c = 0; c < 4; ++c)
@@ -1872,11 +1871,6 @@ ct_status backproject_noalloc(ct_plan *p, ct_backprojector kind, const void *pro
     return launch_backproject(p, kind, proj, pt, vol, vt, accumulate, a0, a1, sl, st, scr, NOALLOC_SCRATCH_BYTES);
 }
 
-bool sart_col_ok(const ct_plan *p) {
-    return !p->views && (lane_voxels(p->g.nVoxel[2]) > 4 ||
-                         std::min<int64_t>(sart_rows(p->g, 1), p->g.nDetector[1] + 4) <= SART_MAX_ROWS);
-}
-
 ct_status launch_sart_update(ct_plan *p, const float *r, float *vol, int64_t a0, int64_t a1, float lambda,
                              hipStream_t st) {
     const AngleGeo *tab = nullptr;
@@ -1896,9 +1890,19 @@ ct_status launch_sart_update_col(ct_plan *p, const float *rT, float *vz, int64_t
     ct_status s = plan_device_table(p, st, &tab);
     if (s != CT_OK) return s;
     BpArgs A = make_bp_args(p, tab, a0, a1, full_slab(p->g), 1);
+    // The rows go through LDS while there are not many more of them than heights, and as few as leave the
+    // blocks their LDS: forming a row costs less than reading a height's taps, but every row is formed and
+    // taps are read for heights alone.  Above, taps per height, 8 heights per lane.  Sweeps of 24 views in
+    // subsets of 8, bound on the rows: LDS / taps us, 64^3 (R = 1) 580: 155 / 156, 730: 187 / 178, 1160: 232 / 196;
+    // 128^3 (R = 2) 1170: 516 / 563, 1460: 666 / 593; 200^3 (R = 4) 1140: 1123 / 1171, 1370: 1334 / 1267, 1600: 1618 /
+    // 1403; 256^3 (R = 4) 1170: 1735 / 1979, 1460: 2297 / 2075.
     int R = lane_voxels(A.nz);
-    while (R > 1 && R <= 4 && sart_rows(p->g, R) > SART_MAX_ROWS) R /= 2;
-    const int hrows = R > 4 ? 0 : (int)std::min<int64_t>(sart_rows(p->g, R), A.nv + 4);
+    int hrows = 0;
+    if (R <= 4) {
+        const int64_t rows = std::min<int64_t>(sart_rows(p->g, R), A.nv + 4);
+        if (rows <= std::min(600 * R, 1200)) hrows = (int)rows;
+        else R = 8;
+    }
     const int zwaves = (A.nz + 64 * R - 1) / (64 * R);
     const int64_t waves = (int64_t)A.nx * A.ny * zwaves;
 #define CT_SART_U(RR)                                                                                                  \

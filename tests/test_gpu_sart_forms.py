@@ -1,0 +1,33 @@
+"""Both forms of the column-major OS-SART update (rows interpolated into LDS, taps read per height) against the
+CPU FP64 oracle, on either side of the bound on the detector rows that separates them for 1, 2 and 4 heights
+per lane."""
+import numpy as np
+import pytest
+import torch
+
+from _helpers import TOL_BP, rel_l2, say
+from paper_1905_03748_amd import inputs
+from paper_1905_03748_amd.operators import Plan
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _work(nz, dz, ndet, dv):
+    return inputs.Workload("sart_forms", (14, 13, nz), (1.5, 1.6, dz), ndet, (2.4, dv), 23, 10, 5,
+                           off_origin=(1.1, -0.6, 3.0), off_detector=(0.4, -0.3))
+
+
+# 64 / 100 / 130 slices take 1 / 2 / 4 heights per lane: up to 600 / 1200 / 1200 rows go through LDS
+@pytest.mark.parametrize("nz,dz,ndet,dv", [
+    (64, 0.9, (9, 900), 0.15), (64, 0.9, (9, 900), 0.14), (64, 0.9, (9, 596), 0.14), (64, 0.9, (9, 597), 0.14),
+    (100, 0.6, (7, 1400), 0.08), (100, 0.6, (7, 1400), 0.07), (130, 0.5, (7, 1300), 0.085), (130, 0.5, (7, 1300), 0.08)])
+def test_sart_forms_match_the_oracle(orc, nz, dz, ndet, dv):
+    w = _work(nz, dz, ndet, dv)
+    say(f"[sart forms] {nz} slices of {dz}, detector {ndet} of {dv}")
+    og = orc.Geometry.from_dict(w.geometry_dict())
+    vol = np.random.default_rng(3).uniform(0, 1, w.nvox[::-1])
+    b = orc.siddon_fwd(og, w.angles, vol).astype(np.float32)
+    got = Plan(w.geometry_dict(), w.angles).sart(torch.from_numpy(b).to(DEV), 2, lam=0.8, block=18)
+    ref = orc.os_sart(og, w.angles, b.astype(np.float64), 2, block=18, lam=0.8)
+    assert rel_l2(got.cpu().numpy(), ref) <= TOL_BP
