@@ -1393,7 +1393,8 @@ __global__ __launch_bounds__(256) void k_sart_update_col(const float *__restrict
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const float *h = hw + clampi(ib[r] - lo, 0, nrow - 2);
-                num[r] += fmaf(fb[r], h[1] - h[0], h[0]);
+                // (weights, not a difference: a row that is infinite adds infinity, not NaN)
+                num[r] += fmaf(fb[r], h[1], (1.0f - fb[r]) * h[0]);
                 if (in) {
                     V[r] += wv;
                 } else {

@@ -1,6 +1,6 @@
 """Both forms of the column-major OS-SART update (rows interpolated into LDS, taps read per height) against the
 CPU FP64 oracle, on either side of the bound on the detector rows that separates them for 1, 2 and 4 heights
-per lane."""
+per lane, and with a pixel that is infinite."""
 import numpy as np
 import pytest
 import torch
@@ -31,3 +31,17 @@ def test_sart_forms_match_the_oracle(orc, nz, dz, ndet, dv):
     got = Plan(w.geometry_dict(), w.angles).sart(torch.from_numpy(b).to(DEV), 2, lam=0.8, block=18)
     ref = orc.os_sart(og, w.angles, b.astype(np.float64), 2, block=18, lam=0.8)
     assert rel_l2(got.cpu().numpy(), ref) <= TOL_BP
+
+
+@pytest.mark.parametrize("nz,dz,ndet,dv", [(64, 0.9, (21, 70), 1.7), (130, 0.5, (21, 90), 1.2), (64, 0.9, (9, 900), 0.14),
+                                           (400, 0.2, (21, 120), 1.1)])
+@pytest.mark.parametrize("bad", [float("inf"), -float("inf")])
+def test_sart_infinite_pixel_stays_infinite(nz, dz, ndet, dv, bad):
+    # the logarithm of an empty count: the voxels it reaches become infinite, none NaN, in one update
+    w = _work(nz, dz, ndet, dv)
+    b = torch.rand((23, ndet[1], ndet[0]), generator=torch.Generator().manual_seed(4))
+    b[5, ndet[1] // 2, ndet[0] // 2] = bad
+    say(f"[sart forms] {nz} slices of {dz}, detector {ndet} of {dv}, {bad}")
+    x = Plan(w.geometry_dict(), w.angles).sart(b.to(DEV), 1, lam=0.8, block=23)
+    assert not bool(torch.isnan(x).any())
+    assert bool((x == bad).any())
