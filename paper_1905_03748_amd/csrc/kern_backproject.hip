@@ -1698,9 +1698,11 @@ ct_status launch_backproject(ct_plan *p, ct_backprojector kind, const void *proj
             // to be those of voxels taken one by one (CGLS on 243 x 251 x 187: 24.0 against 19.4 ms).  The choice
             // does not look at the slab, so a volume cut into slabs gets the bits of the whole one: pairs serve
             // up to 64 slices too, with half of their lanes (64 slices of 256^2 / 30 angles, 2 / 3 / 4 rows
-            // meeting a pair: 183 / 208 / 265 us, one by one with all lanes 256 / 262 / 301).
+            // meeting a pair: 183 / 208 / 265 us, one by one with all lanes 256 / 262 / 301), except in volumes
+            // whose columns do not fill the chip, where a wave's own time counts (64 slices of 64^2 / 80^2, 120
+            // angles, 4 rows meeting a pair: 106 / 136 us, one by one 91 / 152).
             const int nr2 = std::min<int>(p->views ? adj_rows_views(p, 2) : adj_rows(p->g, 2), (int)p->g.nDetector[1] + 2);
-            const bool pairs = slab.pairs && nr2 <= 4;
+            const bool pairs = slab.pairs && nr2 <= 4 && (p->g.nVoxel[2] > 64 || p->g.nVoxel[0] * p->g.nVoxel[1] >= 6400);
             const int64_t nzspan = slab.own_hi - (pairs ? slab.own_lo & ~int64_t(1) : slab.own_lo);
             int R = std::max(lane_voxels(nzspan), pairs ? 2 : 1);
 #ifdef CT_ADJ_R

@@ -1,6 +1,7 @@
 """The exact adjoint of a volume cut into slabs is bit for bit the whole one's: slabs that start on odd and on
 even slices, of fewer and of more than 64 slices, with one and with two slab buffers, where 2, 3 and 4 detector
-rows can meet two neighbouring voxels (they are taken in pairs) and where more can."""
+rows can meet two neighbouring voxels (they are taken in pairs), where more can, and in volumes of up to 64
+slices with few columns (taken one by one) and with many (in pairs)."""
 import pytest
 import torch
 
@@ -26,12 +27,13 @@ def _cap(plan, n_slabs):
     raise AssertionError(f"no cap gives {n_slabs} slabs")
 
 
-# slices, slice height, rows, row pitch
-@pytest.mark.parametrize("nz,dz,nv,dv", [(259, 0.8, 200, 2.6), (259, 0.8, 300, 1.4), (259, 0.8, 420, 0.8),
-                                         (259, 0.8, 500, 0.6), (61, 1.0, 71, 1.6)])
+# columns, slices, slice height, rows, row pitch
+@pytest.mark.parametrize("nxy,nz,dz,nv,dv", [((25, 24), 259, 0.8, 200, 2.6), ((25, 24), 259, 0.8, 300, 1.4),
+                                             ((25, 24), 259, 0.8, 420, 0.8), ((25, 24), 259, 0.8, 500, 0.6),
+                                             ((25, 24), 61, 1.0, 71, 1.6), ((81, 80), 61, 1.0, 71, 1.6)])
 @pytest.mark.parametrize("n_slabs", [3, 4, 9])
-def test_adjoint_slabs_bitwise(nz, dz, nv, dv, n_slabs, monkeypatch):
-    w = inputs.Workload("adj_slabs", (25, 24, nz), (1.4, 1.5, dz), (27, nv), (1.3, dv), 11, 10, 3,
+def test_adjoint_slabs_bitwise(nxy, nz, dz, nv, dv, n_slabs, monkeypatch):
+    w = inputs.Workload("adj_slabs", nxy + (nz,), (1.4, 1.5, dz), (27, nv), (1.3, dv), 11, 10, 3,
                         off_origin=(2.0, -1.0, 0.3), off_detector=(0.31, 0.0))
     plan = Plan(w.geometry_dict(), w.angles + 0.1)
     y = inputs.random_array((11, nv, 27), 6, kind="uniform")
