@@ -1633,21 +1633,20 @@ ct_status launch_forward(ct_plan *p, ct_projector kind, const void *vol, ct_dtyp
         if (vz) {
             const int64_t nu = g.nDetector[0], nv = g.nDetector[1];
             // Neighbouring rows in pairs where the upper row of a pair stays less than two slots above the
-            // lower one, there are enough of them and the blocks fill the chip (1024 of 4 waves, as many as it
-            // holds at once; for 16-bit storage, whose pairs convert twice the values per load, a little more).
+            // lower one, there are enough of them and their waves fill the chip about half (512 blocks of 4
+            // waves' worth of rows; for 16-bit storage, whose pairs convert twice the values per load, 1024).
             // Else rows 64 apart, two per lane when the launch fills the chip with them: a pair's wave works
-            // twice as long, which nothing hides on a chip that is not full, and up to 64 rows leave half of its
-            // lanes idle.  Rows 64 apart / pairs, us: 96^2 x 8 / 32 / 64 views (192 / 768 / 1536 blocks) 31 / 45 /
-            // 82 against 37 / 42 / 64, in FP16 31 / 45 / 84 against 46 / 47 / 68; 128^2 x 16 / 48 views (512 / 1536)
-            // 49 / 97 against 51 / 83, in FP16 46 / 100 against 59 / 94; 256^2 x 1 / 16 views 59 / 231 against 72 /
-            // 181; 65 rows x 64 views (1024 blocks) 42 against 45, 72 rows 50 against 45; 64^3 / 64 views of 64^2 31
-            // against 40.  (FP16 stays uneven up to 4096 blocks: 192^2 and 200^2 at 2100 and 2400 blocks 156 / 183
-            // against 170 / 167.)  The plan's angles are counted, so that a range of them gives the bits of the
-            // whole: a few views of a large plan are projected in pairs.
+            // twice as long, which nothing hides on an empty chip, and up to 64 rows leave half of its lanes
+            // idle.  Rows 64 apart / pairs, us: 96^2 x 8 / 32 / 64 views (144 / 576 / 1152 blocks' worth) 31 / 45 /
+            // 82 against 37 / 42 / 64, in FP16 31 / 45 / 84 against 46 / 47 / 68; 128^2 x 16 / 24 views (512 / 768)
+            // 49 / 60 against 51 / 55, in FP16 46 / 59 against 59 / 63; 256^2 x 1 / 4 / 16 views (128 / 512 / 2048) 59 /
+            // 82 / 231 against 72 / 75 / 181; 65 rows x 64 views of 65^2 42 against 45, 72 rows 50 against 45; 64^3 / 64
+            // views of 64^2 31 against 40.  (FP16 stays uneven up to 4096 blocks: 192^2 and 200^2 at 2100 and 2400
+            // blocks 156 / 183 against 170 / 167.)  The plan's angles are counted, so that a range of them gives
+            // the bits of the whole: a few views of a large plan are projected in pairs.
             const int64_t cblocks = (nu + ZC_COLS - 1) / ZC_COLS;
             const int64_t nang = slab.own_angles ? a1 - a0 : (int64_t)p->angles.size();
-            const bool pair = nv >= 72 && cblocks * ((nv + 127) / 128) * nang >= (vt == CT_F32 ? 1024 : 1280) &&
-                              zpair_ok(p, a0, a1);
+            const bool pair = nv >= 72 && cblocks * nv * nang >= (vt == CT_F32 ? 512 : 1024) * 128 && zpair_ok(p, a0, a1);
             const int rows = pair || cblocks * (a1 - a0) * ((nv + 127) / 128) >= 4096 ? 2 : 1;
             const int64_t rgroups = (nv + 64 * rows - 1) / (64 * rows);
             const int64_t max_ang = angles_per_launch(cblocks * rgroups, 64 * ZC_COLS);

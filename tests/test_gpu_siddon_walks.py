@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _work(nv, dv, offv, nz=40, views=150, nu=33):
+def _work(nv, dv, offv, nz=40, views=210, nu=33):
     return inputs.Workload("walks", (41, 38, nz), (1.0, 1.1, 1.0), (nu, nv), (69.3 / nu, dv), views, 10, 3,
                            off_origin=(2.0, -1.0, 0.7), off_detector=(0.31, offv))
 
@@ -23,7 +23,7 @@ def _volume(w):
 
 
 # rows, row pitch (mm), detector offset (mm), slices: with 1 mm slices the rows lie 0.56 .. 0.78 of the pitch
-# apart in the grid; 9 blocks a view and 128 rows, 1350 and more in all
+# apart in the grid; 9 groups of columns and 210 views, at least 1024 blocks' worth of rows
 @pytest.mark.parametrize("nv,dv,offv,nz", [
     (72, 1.1, 0.0, 40), (73, 1.6, 0.3, 40), (127, 1.6, 0.0, 40), (128, 1.6, 0.4, 40), (129, 1.6, -0.2, 40),
     (130, 2.2, 0.0, 40), (257, 0.7, 0.1, 40), (90, 2.9, 0.0, 40), (78, 1.6, 90.0, 40), (78, 1.6, -90.0, 40),
@@ -51,7 +51,7 @@ def test_pair_walk_matches_the_oracle(orc, nv, dv, offv, nz):
 @pytest.mark.parametrize("at", [(1, 0, 0), (20, 19, 20), (38, 37, 40)])
 @pytest.mark.parametrize("dv", [1.1, 1.6, 2.4])
 def test_pair_walk_non_finite_voxel(orc, at, dv):
-    w = _work(129, dv, 0.0, views=70)   # 1260 blocks
+    w = _work(129, dv, 0.0, views=70)
     vol = _volume(w)
     near = np.zeros(w.nvox[::-1])
     near[max(at[0] - 1, 0):at[0] + 2, at[1], at[2]] = 1.0
@@ -68,7 +68,7 @@ def test_pair_walk_non_finite_voxel(orc, at, dv):
 
 @pytest.mark.parametrize("dt,nv,views,pairs", [
     (torch.float32, 130, 4, False), (torch.float32, 130, 56, False), (torch.float32, 130, 57, True),
-    (torch.float16, 130, 71, False), (torch.float16, 130, 72, True),
+    (torch.float16, 130, 112, False), (torch.float16, 130, 113, True),
     (torch.float32, 71, 300, False), (torch.float32, 72, 300, True)])
 def test_walk_is_chosen_by_the_plan(dt, nv, views, pairs):
     # the first two views of a small and of a large plan are the same rays: the pair walk adds the pieces of a
