@@ -317,9 +317,14 @@ static_assert(BPL_NZ * 256 <= BPL_FLOATS, "the staging window parks the accumula
 #ifndef CT_BPL_WAVES_PM
 #define CT_BPL_WAVES_PM 7
 #endif
-template <int W, int PITCH, typename TP, typename TV>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W == CT_BP_FDK ? CT_BPL_WAVES : CT_BPL_WAVES_PM))) void k_bp_lds(const TP *__restrict__ proj, TV *__restrict__ vol, BpArgs A, int WW,
-                                                int HW, int K) {
+// FEW: launches of up to 1024 blocks, which the chip holds all at once at 4 waves per SIMD: there are no other
+// waves then, so the compiler gets the registers of 4 to keep more reads of one wave in flight (bitwise the same).
+// 8 or 7 waves / 4 waves per SIMD, us: FDK 64^3 / 180 angles 521 / 378, 128^3 / 90 248 / 197, 160^3 (1000 blocks) / 90
+// 257 / 216, 176^3 (1331 blocks) / 90 298 / 308; pseudo-matched 552 / 506, 266 / 256, 308 / 287, 377 / 416.
+#define CT_BPL_OCC __attribute__((amdgpu_waves_per_eu(FEW ? 4 : W == CT_BP_FDK ? CT_BPL_WAVES : CT_BPL_WAVES_PM)))
+template <int W, int PITCH, typename TP, typename TV, bool FEW>
+__global__ __launch_bounds__(256) CT_BPL_OCC void k_bp_lds(const TP *__restrict__ proj, TV *__restrict__ vol, BpArgs A,
+                                                           int WW, int HW, int K) {
     __shared__ float win[BPL_FLOATS];
     __shared__ TileRef ref[BPL_G];
     __shared__ int org[BPL_G][2];
@@ -1644,10 +1649,17 @@ ct_status launch_backproject(ct_plan *p, ct_backprojector kind, const void *proj
         const bool narrow = WW <= BPL_PN;
         const int K = std::min(BPL_K, BPL_FLOATS / ((narrow ? BPL_PN : 64) * HW));
         const dim3 lgrid(grid.x, grid.y, runs(BPL_NZ));
-#define CT_BPL(KIND, PITCH)                                                                                      \
-    CT_DISPATCH2(pt, TP, vt, TV,                                                                                 \
-                 hipLaunchKernelGGL((k_bp_lds<KIND, PITCH, TP, TV>), lgrid, block, 0, st, (const TP *)proj,        \
+        const bool few = (int64_t)lgrid.x * lgrid.y * lgrid.z <= 1024;
+#define CT_BPL2(KIND, PITCH, FEW)                                                                                  \
+    CT_DISPATCH2(pt, TP, vt, TV,                                                                                   \
+                 hipLaunchKernelGGL((k_bp_lds<KIND, PITCH, TP, TV, FEW>), lgrid, block, 0, st, (const TP *)proj,   \
                                     (TV *)vol, A, WW, HW, K))
+#define CT_BPL(KIND, PITCH)          \
+    if (few) {                       \
+        CT_BPL2(KIND, PITCH, true);  \
+    } else {                         \
+        CT_BPL2(KIND, PITCH, false); \
+    }
         if (kind == CT_BP_FDK) {
             if (narrow) {
                 CT_BPL(CT_BP_FDK, BPL_PN);
@@ -1662,6 +1674,7 @@ ct_status launch_backproject(ct_plan *p, ct_backprojector kind, const void *proj
             }
         }
 #undef CT_BPL
+#undef CT_BPL2
         CT_HIP(hipGetLastError());
         return CT_OK;
     }
