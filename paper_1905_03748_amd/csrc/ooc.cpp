@@ -327,7 +327,7 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
     st.t_pin_s += secs(tp, clk::now());
     Events ev_h2d, ev_k, ev_d2h, ev_vol, ev_up, tk0, tk1;
     if ((s = ev_h2d.make(3)) != CT_OK || (s = ev_k.make(3)) != CT_OK || (s = ev_d2h.make(3)) != CT_OK ||
-        (s = ev_vol.make(2)) != CT_OK || (s = ev_up.make(2)) != CT_OK)
+        (s = ev_vol.make(2)) != CT_OK)
         return s;
     tk0.e.resize(nchunks, nullptr);
     tk1.e.resize(nchunks, nullptr);
@@ -392,17 +392,20 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
         };
         if (L.col) {
             // Column-major slab: pieces of ZSTAGE slices through the device stage, transposed into place.
-            // The stage passes between the copy stream and the compute stream by events, and a pageable
-            // volume is copied into one pinned buffer, as many slices at a time as it holds, while the
-            // other is sent, so the host waits for a buffer only (512^3 in two slabs, 60 angles: 62 ->
-            // 29 ms with the rows' copies on threads too, where one thread copied 8 slices, then the host
-            // waited for them and for their transpose).
+            // A pageable volume is copied into one pinned buffer, as many slices at a time as it holds, while
+            // the other is sent; the stage then passes between the copy stream and the compute stream by
+            // events, so the host waits for a buffer only (512^3 in two slabs, 60 angles: 62 -> 29 ms with
+            // the rows' copies on threads too, where one thread copied 8 slices, then the host waited for
+            // them and for their transpose).  A pinned volume has no copies to overlap, and two streams that
+            // wait for each other's events are slower than a host that waits for each piece (400^3 / 8
+            // angles in two slabs 9.6 against 7.8 ms).
             const int64_t nzp = (own_hi - own_lo) + 2;
             const size_t piece = std::max<size_t>(UPLOAD_PIECE, (size_t)ZSTAGE * slice);
             const bool small = (size_t)g.nVoxel[2] * slice < UPLOAD_SMALL;
             const int64_t fit = piece <= STAGE_PIECE && !small ? (int64_t)(piece / slice) / ZSTAGE * ZSTAGE : 0;
-            const bool whole = vol_pinned || fit > 0;  // a pinned buffer holds a piece
-            const int64_t nhost = vol_pinned ? own_hi - own_lo : std::max(fit, ZSTAGE);
+            const bool whole = !vol_pinned && fit > 0;  // a pinned buffer holds a piece
+            if (whole && ev_up.e.empty() && (s = ev_up.make(2)) != CT_OK) return s;
+            const int64_t nhost = whole ? fit : ZSTAGE;
             bool used[2] = {false, false}, staged = false;
             int q = 0;
             auto transpose = [&](int64_t z0, int64_t zn) -> ct_status {
@@ -425,7 +428,7 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
             for (int64_t h0 = own_lo; h0 < own_hi; h0 += nhost) {
                 const int64_t hn = std::min(nhost, own_hi - h0);
                 const char *from = (const char *)h_vol + h0 * slice;
-                if (!vol_pinned && whole) {
+                if (whole) {
                     if (used[q]) CT_HIP(hipEventSynchronize(ev_vol.e[q]));
                     auto b = clk::now();
                     par_memcpy(svol[q].p, from, (size_t)hn * slice);
@@ -443,7 +446,7 @@ ct_status ooc_forward(ct_plan *p, ct_projector kind, const void *h_vol, ct_dtype
                     }
                     if ((s = transpose(z0, zn)) != CT_OK) return s;
                 }
-                if (!vol_pinned && whole) {
+                if (whole) {
                     CT_HIP(hipEventRecord(ev_vol.e[q], S.h2d));
                     used[q] = true;
                     q ^= 1;
