@@ -131,7 +131,9 @@ ct_status ct_forward(ct_plan *plan, ct_projector projector, const void *d_vol, c
 
 /* Backprojection vol = B proj (or vol += B proj) over the angles [angle_begin, angle_end)
  * (Section 2.2; one thread per voxel column segment, loops over angles).  Layouts and errors as
- * ct_forward, with the roles of the arrays swapped. */
+ * ct_forward, with the roles of the arrays swapped.  A pixel that is not finite reaches the voxels
+ * its ray meets; with CT_BP_ADJOINT it can also make voxels up to three slices above and below them
+ * NaN (their sums include it times a length of zero). */
 ct_status ct_backproject(ct_plan *plan, ct_backprojector backprojector, const void *d_proj,
                          ct_dtype proj_dtype, void *d_vol, ct_dtype vol_dtype, int accumulate,
                          int64_t angle_begin, int64_t angle_end, void *stream);
@@ -204,7 +206,9 @@ ct_status ct_backproject_host(ct_plan *plan, ct_backprojector backprojector, con
  * not be used concurrently by another call. */
 
 /* CGLS (Bjorck) with A = CT_SIDDON and A^T = CT_BP_ADJOINT over all plan angles: from the
- * initial d_x, minimises ||A x - b||.  x is stored in vol_dtype and b in proj_dtype; the
+ * initial d_x, minimises ||A x - b||.  Its adjoint sums voxel by voxel, where ct_backproject may take
+ * two neighbouring ones together: the two round differently (about 1e-7, relative), neither being
+ * closer to the exact transpose.  x is stored in vol_dtype and b in proj_dtype; the
  * recurrence vectors (r, q projection-shaped; s, p volume-shaped) are FP32, because CGLS search
  * directions are unnormalised and overflow FP16's range on realistic problems.  Inner products,
  * step sizes and the residual-norm recurrence rho_{k+1} = rho_k - alpha_k gamma_k are FP64.

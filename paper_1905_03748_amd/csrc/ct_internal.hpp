@@ -97,9 +97,9 @@ struct Slab {
     bool scratch_ok;   // the launch may allocate device scratch (resident calls; not under a cap)
     bool zcol = false; // exact-adjoint backprojection only: the slab is column-major, [y][x][mem_n]
     bool no_alloc = false;  // the launch allocates nothing (the angle table must be on the device)
-    // exact-adjoint backprojection only: voxels may be taken in pairs, whose faces are rounded otherwise.  CGLS,
-    // whose recurrences carry 1e-10 of a difference in its first gradient to 1e-8 in its 64-bit residuals, takes
-    // each alone.
+    // exact-adjoint backprojection only: voxels may be taken in pairs, whose faces are rounded otherwise (both
+    // ways are as far from the exact adjoint).  CGLS takes each alone: its recurrences carry 1e-10 of a
+    // difference in the first gradient to 6e-9 in the residual norms, and those are to stay what they were.
     bool pairs = true;
     // Siddon only: the walk is chosen for the launch's own angles; else for the plan's, so that any range of them
     // gives the bits of the whole
@@ -121,8 +121,8 @@ inline Slab full_slab(const ct_geometry &g) {
 // angles [a0, a1) starting at projection 0).
 // vcopy: optional copy of vol in the layout the projector reads, kept by the caller (then no
 // scratch copy is made): for Siddon the column-major slots of launch_zcols (for a slab launch:
-// its mem_n slices, mem_n + 2 slots per column; with the guard elements of zcol_base), for the interpolated projector the [z][x][y]
-// transpose of launch_transpose_xy.
+// its mem_n slices, mem_n + 2 slots per column; with the guard elements of zcol_base), for the
+// interpolated projector the [z][x][y] transpose of launch_transpose_xy.
 ct_status launch_forward(ct_plan *p, ct_projector kind, const void *vol, ct_dtype vt, void *proj,
                          ct_dtype pt, int accumulate, int64_t a0, int64_t a1, const Slab &slab,
                          hipStream_t st, const void *vcopy = nullptr);

@@ -770,8 +770,8 @@ __global__ __launch_bounds__(256) void k_adj_prep(const TP *__restrict__ proj, f
 // Rows of either sign may meet a pair at the source plane, so faces are taken in index order and a row's
 // overlap is the distance of its clamped crossings (ORD is not used).  The parameters are formed from the
 // shared face, so each voxel has one face as exact as alone and one a single rounding off, as alone.
-// 512^3 / 360 angles 33.0 -> 28.3 ms, helical 256^3 / 180 2.5 -> 1.8 ms, the gradient of 128^3 / 90 angles
-// 394 -> 335 us.
+// 512^3 / 180 angles 16.6 -> 14.1 ms, helical 18.9 -> 14.4 ms, 256^3 / 60 angles 0.76 -> 0.61 ms, the gradient of
+// 128^3 / 90 angles 394 -> 334 us.
 template <typename TV, int R, int NR, bool ZC, bool ORD, bool VW = false, bool PAIR = false>
 __global__ __launch_bounds__(256) CT_ADJ_OCC void k_adj_col(const float *__restrict__ yq, TV *__restrict__ vol, BpArgs A,
                                                  int zgroups, int xblocks) {
@@ -1708,7 +1708,9 @@ ct_status launch_backproject(ct_plan *p, ct_backprojector kind, const void *proj
         if (nr <= 4 && yq && qcap >= per_angle) {
             const int64_t kq = std::min<int64_t>(a1 - a0, (int64_t)(qcap / per_angle));
             // Pairs of voxels where the rows that can meet two fit one 16-byte load, unless the caller's sums are
-            // to be those of voxels taken one by one (CGLS on 243 x 251 x 187: 24.0 against 19.4 ms).  The choice
+            // to be those of voxels taken one by one (Slab::pairs; CGLS on 243 x 251 x 187 takes 24.0 ms, with
+            // pairs it would 19.4).  Four rows meeting a pair still pay where two meet one voxel (256^3 / 60
+            // angles 0.91 -> 0.78 ms, 384^3 2.50 -> 2.44, 512^3 / 30 3.07 either way).  The choice
             // does not look at the slab, so a volume cut into slabs gets the bits of the whole one: pairs serve
             // up to 64 slices too, with half of their lanes (64 slices of 256^2 / 30 angles, 2 / 3 / 4 rows
             // meeting a pair: 183 / 208 / 265 us, one by one with all lanes 256 / 262 / 301), except in volumes

@@ -669,7 +669,7 @@ __global__ __launch_bounds__(64 * ZC_COLS) void k_siddon_col(const TV *__restric
 // before and after (for the first and last column the copy's guard elements), nz + 3 is loaded where lo =
 // nz and taken as zero.
 //
-// Bound: the address unit (82 % busy, 20 cycles per load) and VALU issue (28 instructions per load of two
+// Bound: the address unit (85 % busy, 20 cycles per load) and VALU issue (28 instructions per load of two
 // rows) about evenly, with 124 GB per launch past L2 (6 TB/s) at 512^3 / 360 angles: 26.9 -> 20.9 ms there
 // (2.3e12 voxel projections per second), 243 x 251 x 187 / 175 angles of 301 x 233 1.86 -> 1.56 ms.
 #ifndef CT_ZP_BATCH
@@ -1686,10 +1686,10 @@ ct_status launch_forward(ct_plan *p, ct_projector kind, const void *vol, ct_dtyp
 #define CT_IC_XPAIR_MAX (size_t(16) << 30)
 #endif
         const bool xp = 2 * pbytes <= CT_IC_XPAIR_MAX;
-        // cell offsets in 32 bits: the paired copy below 4 GiB, a padded slice within the 24-bit multiply
-        // 32-bit cells up to 1 GiB: larger copies are bound by what leaves L2, and lanes running on past their
-        // last sample add to it (FP32, 448^3 / 200 angles, 0.73 GB: 43.8 -> 40.1 ms; 512^3 / 360, 1.09 GB:
-        // 107 -> 111 ms; FP16 512^3 / 180, 0.55 GB: 57 -> 48 ms)
+        // Cell offsets in 32 bits for paired copies below 1 GiB whose padded slice fits the 24-bit multiply:
+        // larger copies are bound by what leaves L2, and lanes running on past their last sample add to it
+        // (FP32, 448^3 / 200 angles, 0.73 GB: 43.8 -> 40.1 ms; 512^3 / 360, 1.09 GB: 107 -> 111 ms; FP16
+        // 512^3 / 180, 0.55 GB: 57 -> 48 ms).
         const bool c32 = xp && 2 * pbytes < (size_t(1) << 30) && (nx + 3) * (nz + 3) < (1 << 23);
         void *vpad = nullptr;
         if (CT_MALLOC_ASYNC(&vpad, xp ? 2 * pbytes : pbytes, st) == hipSuccess) {

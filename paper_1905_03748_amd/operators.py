@@ -159,7 +159,8 @@ class Plan:
     def cgls(self, b: torch.Tensor, niter: int, x: torch.Tensor | None = None, vol_dtype=None,
              resid: torch.Tensor | None = None, workspace: torch.Tensor | None = None, stream=None):
         """Runs CGLS in place on x (zeros if None); returns (x, resid) with resid a device FP64
-        tensor of niter+1 residual norms."""
+        tensor of niter+1 residual norms.  Its adjoint sums voxel by voxel and so rounds a little
+        differently from backproject(kind="adjoint"), which may take two neighbouring ones together."""
         if x is None:
             x = torch.zeros(self.vol_shape, dtype=vol_dtype or b.dtype, device=b.device)
         if workspace is not None:
