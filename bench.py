@@ -5,13 +5,14 @@ the FDK-weighted backprojector) on the 512^3 workload: p = A x (Siddon, 360 angl
 then v = B p (voxel-driven FDK backprojection), inputs resident in HBM.  value = 2 * Nx Ny Nz N_angles
 / step time, in Gvoxel.proj/s.  Prints one JSON line.
 
-The roofline entry is for the dominant kernel of the step, with algorithmic bytes under the
-gather model (bytes each unit of work must read if nothing were reused):
+The roofline entry is for the dominant kernel of the step.  It is headed by what the committed counter
+record says: the unit the counters show busiest, and the bytes that leave L2 per launch over the
+kernel's average duration measured with HIP events on its stream, against the HBM peak.  Beside it
+stand the bytes under the gather model (what each unit of work must read if nothing were reused):
   Siddon forward      segments * 4 B, 1.133 segments per voxel.proj at this workload
   FDK backprojection  4 bilinear taps * 4 B = 16 B per voxel.proj
-divided by the kernel's average duration measured with HIP events on its stream.  The model counts no
-reuse, so the caches can carry a kernel past 100 % of it; the bytes that actually leave L2, and the
-unit that the counters show busiest, are printed beside it from the committed counter record.
+The model counts no reuse, so the caches carry a kernel past 100 % of it; it heads the entry only
+where no counter record of the current sources exists.
 """
 from __future__ import annotations
 
@@ -599,12 +600,13 @@ def main():
                 "siddon_fwd_gvps": round(vp / (fwd_ms * 1e-3) / 1e9, 2),
                 "fdk_bp_gvps": round(vp / (bp_ms * 1e-3) / 1e9, 2)},
         "roofline": {"bound": "hbm",
-                     "kernel": "k_siddon_pair<float, float>" if dom == "siddon" else "k_bp_lds<0, 37, float, float>",
+                     "kernel": "k_siddon_pair<float, float>" if dom == "siddon" else "k_bp_lds<0, 37, float, float, false>",
                      "byte_model": "gather model: %s B per voxel.proj x %.4g voxel.proj per launch"
                                    % (round(BYTES_PER_VP[dom], 3), vp),
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None},
     }
+    gather = {k: out["roofline"][k] for k in ("byte_model", "achieved", "frac")}
     rec = recorded_traffic("siddon_fwd" if dom == "siddon" else "fdk_bp")
     if rec is not None:
         gb = (rec["read_bytes"] + rec["write_bytes"]) / 1e9
@@ -619,6 +621,8 @@ def main():
         busy = {"texture_address_unit": rec["ta_busy"], "vector_alu": rec["valu"], "l2_miss_bytes_vs_hbm_peak": round(miss, 3)}
         rl["limiter"] = {"unit": max(busy, key=busy.get), "busy": busy, "l2_hit": rec["l2_hit"],
                          "counters_avg_ms": rec["avg_ms"]}
+        rl.update(bound=rl["limiter"]["unit"], byte_model="measured: GB per launch past L2 (traffic)",
+                  achieved=round(gb / (dom_ms * 1e-3), 1), frac=round(miss, 4), gather_model=gather)
 
     if not args.no_extras:
         def timed(fn, reps=3):
